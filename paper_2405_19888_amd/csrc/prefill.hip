@@ -169,7 +169,7 @@ __device__ __forceinline__ void prefill_prefix_item(const PrefillArgs& a, char* 
   TileJob j;
   j.q = a.q; j.pk = a.pk; j.pv = a.pv; j.npool = a.npblk; j.H = a.H; j.h = h;
   j.t0 = t0; j.t1 = t1; j.o_part = a.o_part; j.lse_part = a.lse_part;
-  j.seg = a.seg; j.slot = lvl * a.seg_p + c; j.scale_log2 = a.scale_log2; j.lim_min = 0;
+  j.seg = a.seg; j.slot = lvl * a.seg_p + c; j.scale_log2 = a.scale_log2;
   if constexpr (DT == kF32)
     tile_core<DT, D, false>(j, tl, nq);
   else
@@ -210,7 +210,7 @@ __device__ __forceinline__ void prefill_own_item(const PrefillArgs& a, char* lds
   TileJob j;
   j.q = a.q; j.pk = a.sk; j.pv = a.sv; j.npool = a.nsblk; j.H = a.H; j.h = h;
   j.t0 = t0; j.t1 = t1; j.o_part = a.o_part; j.lse_part = a.lse_part;
-  j.seg = a.seg; j.slot = a.seg_pre + k; j.scale_log2 = a.scale_log2; j.lim_min = pos0;
+  j.seg = a.seg; j.slot = a.seg_pre + k; j.scale_log2 = a.scale_log2;
   if constexpr (DT == kF32)
     tile_core<DT, D, true>(j, tl, nq);
   else
@@ -279,7 +279,7 @@ __device__ __forceinline__ void prefill_single_group_item(const PrefillArgs& a, 
   TileJob j;
   j.q = a.q; j.pk = a.pk; j.pv = a.pv; j.npool = a.npblk; j.H = a.H; j.h = h;
   j.t0 = 0; j.t1 = P; j.o_part = nullptr; j.lse_part = nullptr;
-  j.seg = 0; j.slot = 0; j.scale_log2 = a.scale_log2; j.lim_min = 0;
+  j.seg = 0; j.slot = 0; j.scale_log2 = a.scale_log2;
   const WideSingle sg{a.sk, a.sv, a.stab, a.sstride, a.nsblk, runs, tl.count[1], a.out, a.lse};
   wide_tile_single<DT, D>(j, tl, nq, sg);
 }
@@ -313,7 +313,7 @@ __device__ __forceinline__ void prefill_single_own_item(const PrefillArgs& a, ch
   TileJob j;
   j.q = a.q; j.pk = a.sk; j.pv = a.sv; j.npool = a.nsblk; j.H = a.H; j.h = h;
   j.t0 = 0; j.t1 = 0; j.o_part = nullptr; j.lse_part = nullptr;  // no prefix range
-  j.seg = 0; j.slot = 0; j.scale_log2 = a.scale_log2; j.lim_min = 0;
+  j.seg = 0; j.slot = 0; j.scale_log2 = a.scale_log2;
   const WideSingle sg{a.sk, a.sv, a.stab, a.sstride, a.nsblk, runs, 1, a.out, a.lse};
   wide_tile_single<DT, D>(j, tl, nq, sg);
 }

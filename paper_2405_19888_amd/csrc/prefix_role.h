@@ -160,7 +160,6 @@ struct TileJob {
   float* o_part; float* lse_part; // partial results [rows][H][seg][D], [rows][H][seg]
   int seg, slot;                  // slots per (row, head); this tile's slot
   float scale_log2;
-  int lim_min;                    // causal tiles: the smallest row limit (tl.lim)
 };
 
 // The attention core of a query tile: up to 64 query rows (tl.rows, nq of
