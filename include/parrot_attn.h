@@ -311,24 +311,26 @@ parrot_status parrot_validate_nested_inputs(
  * keys.
  *
  * Rows are computed in tiles of 128 (fp16 / bf16 caches) or 64 (fp32) on
- * MFMA, with K/V staged in LDS.  Two plans, chosen per call:
- *   single pass (flat groups, 16-bit caches, prefix and own lengths that fit
- *     one chunk of 8192 tokens and enough tiles to fill the device): one
- *     kernel; a tile of the rows of a group's members (all requests reading
- *     the prefix, stacked) sees the whole prefix and then, request by
- *     request, its rows' own tokens up to their positions; ungrouped
- *     requests' tiles see their own tokens; the output is written directly
- *     and the workspace is not used;
+ * MFMA, with K/V staged in LDS.  Two kinds of plan, chosen per call:
+ *   single pass (flat groups, 16-bit caches, prefix and own lengths of at most
+ *     8192 tokens): one kernel that writes the output directly and leaves the
+ *     workspace unused.  Either a tile of the rows of a group's members (all
+ *     requests reading the prefix, stacked) sees the whole prefix and then,
+ *     request by request, its rows' own tokens up to their positions, and
+ *     ungrouped requests' tiles see their own tokens; or every tile holds rows
+ *     of one request, which see the prefix and then their own tokens (short
+ *     prefixes, where reading them per request costs less than the rest);
  *   split: prefix items (stacked rows against one prefix chunk) and own
  *     items (one request's rows against one chunk of its own tokens, per-row
  *     causal limit) write partial results to the workspace, then the merge
  *     kernel combines them per (row, head).
- * parrot_prefill_single_pass tells which one a call takes.  The environment
- * variable PARROT_PREFILL_SINGLE_PASS=0 forces the split plan; =1 takes the
- * single pass wherever the groups are flat, the caches 16-bit and the lengths
- * at most 8192 (even when the split plan would cut them into chunks to fill
- * the device); other values leave the choice to the plan.  Both plans give
- * the same results to rounding.
+ * The single pass is taken where an estimate from the sizes in `p` and `rows`
+ * expects it to be faster; parrot_prefill_single_pass tells which one a call
+ * takes.  The environment variable PARROT_PREFILL_SINGLE_PASS=0 forces the
+ * split plan; =1 takes the single pass of stacked rows and =2 that of one
+ * request per tile wherever the groups are flat, the caches 16-bit and the
+ * lengths at most 8192; other values leave the choice to the estimate.  All
+ * plans give the same results to rounding.
  *
  *   rows                 (host) row counts; see parrot_prefill_rows
  *   q                    [T][H][D] dtype, 16-byte aligned

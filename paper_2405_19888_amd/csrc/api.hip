@@ -553,20 +553,18 @@ constexpr int kPrefillChunkMin = 256;
 struct PrefillPlan {
   int depth, cp, co, seg_p, seg_pre, seg_s, seg, qtiles_p, qtiles_o;
   long n_pre, n_own;
-  bool single;   // single-pass items: no partial results, no merge
+  int kind;      // PrefillPlanKind; the single-pass kinds have no partial results and no merge
   size_t o_bytes, lse_bytes, info_bytes, total_bytes;
 };
 
-// The single-pass prefill runs when the groups are flat, the caches 16-bit and
-// the prefix and own ranges each fit one chunk of the split plan.
-// PARROT_PREFILL_SINGLE_PASS=0 turns it off; =1 takes it whenever the ranges
-// fit the tile's block table (8192 tokens), even where the split plan would
-// cut them into chunks to fill the device (for tests and tuning).
-// Any other value (or none) leaves the choice to the plan.
+// PARROT_PREFILL_SINGLE_PASS=0 turns the single-pass plans off; =1 takes the
+// stacked one and =2 the per-request one wherever the groups are flat, the
+// caches 16-bit and the ranges fit the tile's block table (8192 tokens), for
+// tests and tuning.  Any other value (or none) leaves the choice to the cost
+// estimate below.
 int single_pass_setting() {
   const char* e = std::getenv("PARROT_PREFILL_SINGLE_PASS");
-  if (e && e[0] == '0' && e[1] == 0) return 0;
-  if (e && e[0] == '1' && e[1] == 0) return 1;
+  if (e && e[0] >= '0' && e[0] <= '2' && e[1] == 0) return e[0] - '0';
   return -1;
 }
 
@@ -579,6 +577,67 @@ int prefill_chunk(long len, double items_per_chunk) {
   while (c > kPrefillChunkMin && c / 2 >= len) c /= 2;
   const double cus = num_cus();
   while (c > kPrefillChunkMin && items_per_chunk * (double)ceil_div(len, c) < 3 * cus) c /= 2;
+  return c;
+}
+
+// Estimated microseconds of the three plans for a 16-bit call on flat groups,
+// from the bounds the host knows.  The figures are fits to sweeps on MI355X
+// (1-64 requests of 1-4000 rows, prefixes of 100-6000 tokens, 8 and 32 heads):
+//  * a workgroup alone on its CU takes 0.8 us per 16 KiB stage of keys, and up
+//    to three on a CU finish a stage every 0.28 + 0.05 w us together, w the
+//    waves with rows (0.33 with one, 0.48 with four);
+//  * a tile's set-up and output cost 1 + 0.9 w us of its CU (6 us of latency), each run of rows
+//    after a stacked tile's first 1 us (2.5 us of latency);
+//  * a launch takes 5 us, the merge of the split plan 4 us more and its partial
+//    results (written, then read) pass at 4.5 TB/s (10 within the 256 MB cache).
+// Measured, split / stacked / per request: 16 requests of 16-64 rows on a
+// 100-token prefix 24 / 26 / 15 us; 64 of 16-64 on 600 tokens 104 / 59 / 84; 64
+// of 1-8 on 2000 tokens 51 / 113 / 173; one prompt of 2000 tokens 75 / 59 / 60;
+// one of 300 tokens 18 / 12 / 13; 64 of 100-300 on 600 408 / 239 / 229.
+struct PrefillCosts { double split, stacked, direct; };
+
+PrefillCosts prefill_costs(const parrot_problem* p, const parrot_prefill_rows* rows,
+                           const PrefillPlan& pl) {
+  const double H = p->num_heads, R = p->num_requests, T = rows->num_query_rows, cus = num_cus();
+  const double st = 4096.0 / p->head_dim;                  // tokens per stage
+  const double tile = parrot::kWideRows;
+  const double mean_q = T / R;
+  const double waves = std::min(4.0, std::ceil(mean_q / 32.0));
+  const double per_stage = 0.28 + 0.05 * waves, setup = 1.0 + 0.9 * waves;
+  const double full_stage = 0.48, full_setup = 4.6;        // tiles of stacked rows
+  // own tokens a tile sees on average: half a whole prompt (plus the tile's
+  // own diagonal), or a share of the longest continued one
+  const bool whole = rows->max_query_rows >= p->max_suffix_len;
+  const double own = std::min<double>(p->max_suffix_len,
+                                      !whole ? 0.6 * p->max_suffix_len
+                                             : mean_q > tile ? (mean_q + tile) / 2 : mean_q);
+  const double own_stages = std::ceil(own / st), max_own = std::ceil(p->max_suffix_len / st);
+  const double pre_stages = p->num_groups > 0 ? std::ceil(p->max_prefix_len / st) : 0.0;
+  const double tiles_o = R * std::max(1.0, mean_q / tile + (mean_q > tile ? 0.5 : 0.0));
+  const double tiles_p = pl.qtiles_p > 0 ? std::max(T / tile + 0.5 * p->num_groups, (double)pl.qtiles_p) : 0.0;
+  // the longest tile alone and the load per CU hide most of each other
+  auto both = [](double latency, double load) {
+    return std::max(6.0 + latency, load) + 0.2 * std::min(6.0 + latency, load);
+  };
+  PrefillCosts c;
+  c.direct = 5.0 + both(0.8 * (pre_stages + max_own),
+                        H * tiles_o / cus * ((pre_stages + own_stages) * per_stage + setup));
+  if (tiles_p > 0) {
+    const double runs = 1.0 + std::min(tile, (double)rows->max_group_rows) / mean_q;
+    c.stacked = 5.0 + both(0.8 * pre_stages + runs * (0.8 * own_stages + 2.5),
+                           H * tiles_p / cus * ((pre_stages + runs * own_stages) * full_stage +
+                                                full_setup + runs));
+  } else {
+    c.stacked = c.direct;
+  }
+  const double slots = pl.seg_p + std::max(1.0, pl.seg_s * own / std::max(1, p->max_suffix_len));
+  const double partial_bytes = 2.0 * T * H * slots * p->head_dim * 4.0;
+  // (its own items run head after head: the last head's long ones end alone)
+  const double item_own = std::min(max_own, pl.co / st);
+  c.split = 9.0 + partial_bytes / (partial_bytes < 2.5e8 ? 10e6 : 4.5e6) + 0.12 * item_own +
+            both(0.8 * std::max(std::min(pre_stages, pl.cp / st), item_own),
+                 H * tiles_p / cus * (pre_stages * full_stage + pl.seg_p * full_setup) +
+                     H * tiles_o / cus * (own_stages * per_stage + setup));
   return c;
 }
 
@@ -632,10 +691,18 @@ parrot_status check_prefill(const parrot_problem* p, const parrot_prefill_rows* 
   pl->n_own = (long)p->num_requests * pl->seg_s * pl->qtiles_o;
   const int setting = single_pass_setting();
   const bool fits = p->max_prefix_len <= kPrefillChunkMax && p->max_suffix_len <= kPrefillChunkMax;
-  pl->single = p->dtype != PARROT_DTYPE_F32 && !nested && fits &&
-               (setting == 1 || (setting == -1 && pl->seg_p <= 1 && pl->seg_s == 1));
-  if (pl->single) {   // one item per group tile (whole prefix), one per own tile
-    pl->n_pre = pl->seg_p > 0 ? (long)p->num_groups * pl->qtiles_p : 0;
+  const bool can = p->dtype != PARROT_DTYPE_F32 && !nested && fits;
+  if (can && setting >= 1) {
+    pl->kind = setting;
+  } else if (can && setting == -1) {
+    // the single-pass plans where they are expected to be clearly faster
+    const PrefillCosts c = prefill_costs(p, rows, *pl);
+    const double best = std::min(c.stacked, c.direct);
+    if (best < 0.9 * c.split)
+      pl->kind = c.direct < c.stacked ? parrot::kPrefillDirect : parrot::kPrefillStacked;
+  }
+  if (pl->kind != parrot::kPrefillSplit) {   // one item per group tile (whole prefix), one per own tile
+    pl->n_pre = pl->kind == parrot::kPrefillStacked && pl->seg_p > 0 ? (long)p->num_groups * pl->qtiles_p : 0;
     pl->n_own = (long)p->num_requests * pl->qtiles_o;
   }
   const long grid = 8L * ceil_div(H, 8) * (pl->n_pre + pl->n_own);
@@ -705,15 +772,15 @@ parrot_status prefill(const parrot_problem* p, const parrot_prefill_rows* rows, 
     a.seg = pl.seg; a.seg_p = pl.seg_p; a.seg_pre = pl.seg_pre; a.seg_s = pl.seg_s;
     a.cp = pl.cp; a.co = pl.co; a.qtiles_p = pl.qtiles_p; a.qtiles_o = pl.qtiles_o;
     a.n_pre = (int)pl.n_pre; a.n_own = (int)pl.n_own;
-    a.meta_wgs = pl.single ? 0 : (T + 255) / 256;
+    a.meta_wgs = pl.kind != parrot::kPrefillSplit ? 0 : (T + 255) / 256;
     a.scale_log2 = p->sm_scale * parrot::kLog2e;
-    a.single = pl.single ? 1 : 0;
+    a.plan = pl.kind;
     a.out = out; a.lse = lse;
     PARROT_TRY(launched(parrot::launch_prefill(a, (int)p->dtype, p->head_dim, s, ev(tr.partials_start),
                                                ev(tr.partials_stop)),
                         "prefill kernel"));
   }
-  if (pl.single) {
+  if (pl.kind != parrot::kPrefillSplit) {
     // no merge: its trace events, if asked for, bracket nothing
     if (tr.merge_start) PARROT_TRY(hip_ok(hipEventRecord(ev(tr.merge_start), s), "hipEventRecord"));
     if (tr.merge_stop) PARROT_TRY(hip_ok(hipEventRecord(ev(tr.merge_stop), s), "hipEventRecord"));
@@ -747,7 +814,7 @@ int parrot_prefill_single_pass(const parrot_problem* p, const parrot_prefill_row
   PrefillPlan pl;
   if (check_prefill(p, rows, nested != 0, &pl) != PARROT_OK) return -1;
   g_err.clear();
-  return pl.single ? 1 : 0;
+  return pl.kind != parrot::kPrefillSplit ? 1 : 0;
 }
 
 parrot_status parrot_shared_prefix_prefill(

@@ -27,7 +27,12 @@
 // tile (g, head h, row tile qt) takes the same stacked rows as a prefix item,
 // sees the whole prefix and then, run by run, each of its requests' own
 // tokens up to its rows' positions, and writes the rows' output; tiles of
-// ungrouped requests see only their own tokens.
+// ungrouped requests see only their own tokens.  A stacked tile's runs follow
+// one another (each at least one stage and a refill of the stage ring, about
+// 2.3 us), so where requests bring few rows and the prefix is short the
+// per-request plan is faster: every tile holds rows of one request and reads
+// the prefix itself (64 requests of 16-64 rows on a 100-token prefix: stacked 39
+// us, per request 42; 16 of them 26 against 15; 16 of 1-8 rows 40 against 10).
 //
 // Work items are placed per XCD (workgroup b runs on XCD b mod 8): XCD x takes
 // every item of heads x, x + 8, ..., one head after another (split plan: a
@@ -289,17 +294,20 @@ __device__ __forceinline__ void prefill_single_group_item(const PrefillArgs& a, 
   wide_tile_single<DT, D>(j, tl, nq, sg);
 }
 
-// Single-pass own tile (request r, row tile t, head h) of a request outside
-// the groups: its rows against its own tokens, causal; writes their output.
-// Grouped requests' rows belong to their group's tiles.
-template <int DT, int D>
+// Single-pass request tile (request r, row tile t, head h): the rows against
+// the prefix of the request's group, if it has one and DIRECT is set, and its
+// own tokens, causal; writes their output.  Without DIRECT the grouped
+// requests' rows belong to their group's tiles.
+template <int DT, int D, bool DIRECT>
 __device__ __forceinline__ void prefill_single_own_item(const PrefillArgs& a, char* lds, int h,
                                                         int r, int t) {
   if (r >= a.R) return;
+  // the request's lengths and group in one round of loads
   const int g = a.gid[r];
-  if (g >= 0 && g < a.NG) return;
-  constexpr int ROWS = kWideRows;
   const ReqRows rw = req_rows(a, r);
+  const bool grouped = g >= 0 && g < a.NG;
+  if (!DIRECT && grouped) return;
+  constexpr int ROWS = kWideRows;
   const int row0 = t * ROWS;
   if (row0 >= rw.count) return;
   const int nq = min(ROWS, rw.count - row0);
@@ -307,6 +315,14 @@ __device__ __forceinline__ void prefill_single_own_item(const PrefillArgs& a, ch
   const TileLds tl = prefill_lds<DT>(lds);
   int2* runs = prefill_runs(lds);
   const int tid = threadIdx.x;
+  int P = 0;
+  if constexpr (DIRECT) {
+    if (grouped) {
+      P = clampi(a.plen[g], 0, a.max_p);
+      const int* tbl = a.ptab + (long)g * a.pstride;
+      for (int i = tid; i < (P + kBlock - 1) / kBlock; i += 256) tl.tbl[i] = clampi(tbl[i], 0, a.npblk - 1);
+    }
+  }
   if (tid < nq) {
     tl.rows[tid] = rw.start + row0 + tid;
     tl.lim[tid] = pos0 + tid;
@@ -314,8 +330,8 @@ __device__ __forceinline__ void prefill_single_own_item(const PrefillArgs& a, ch
   if (tid == 0) runs[0] = int2{r, 0};
   __syncthreads();
   TileJob j;
-  j.q = a.q; j.pk = a.sk; j.pv = a.sv; j.npool = a.nsblk; j.H = a.H; j.h = h;
-  j.t0 = 0; j.t1 = 0; j.o_part = nullptr; j.lse_part = nullptr;  // no prefix range
+  j.q = a.q; j.pk = a.pk; j.pv = a.pv; j.npool = a.npblk; j.H = a.H; j.h = h;
+  j.t0 = 0; j.t1 = P; j.o_part = nullptr; j.lse_part = nullptr;
   j.seg = 0; j.slot = 0; j.scale_log2 = a.scale_log2;
   const WideSingle sg{a.sk, a.sv, a.stab, a.sstride, a.nsblk, runs, 1, a.out, a.lse};
   wide_tile_single<DT, D>(j, tl, nq, sg);
@@ -323,11 +339,12 @@ __device__ __forceinline__ void prefill_single_own_item(const PrefillArgs& a, ch
 
 // Occupancy: three waves per SIMD (three workgroups per CU: 3 x 51 KiB of
 // LDS, at most 168 registers per lane), for either tile core.
-// SINGLE: single-pass items (16-bit caches); otherwise prefix and own items
-// with partial results and row descriptors for the merge.
-template <int DT, int D, bool SINGLE>
+// PLAN: single-pass items, stacked or per request (16-bit caches); otherwise
+// prefix and own items with partial results and row descriptors for the merge.
+template <int DT, int D, int PLAN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void k_prefill(PrefillArgs a) {
+  constexpr bool SINGLE = PLAN != kPrefillSplit;
   static_assert(!SINGLE || DT != kF32, "single-pass tiles are the 16-bit wide tiles");
   __shared__ __attribute__((aligned(1024))) char lds[DT == kF32 ? kPrefillLdsF32 : kPrefillLds];
   static_assert(sizeof(lds) >= tile_lds_bytes(kPrefillMaxBlocks, kTileRows<DT>, kTileRing<DT>),
@@ -343,14 +360,14 @@ void k_prefill(PrefillArgs a) {
     // group tiles head after head, then the own tiles request after request
     const int J = (a.H - x + kXcds - 1) / kXcds;
     const int own = l - J * a.n_pre;
-    if (own < 0) {
+    if (PLAN == kPrefillStacked && own < 0) {
       prefill_single_group_item<DT, D>(a, lds, x + kXcds * (l / a.n_pre), l % a.n_pre);
     } else if (own < J * a.n_own) {
       // a request's last row tiles (the longest causal ranges) first and its
       // heads together, so that no long tile starts when the others end
       const int i = own / J;
       const int r = i / a.qtiles_o, t = a.qtiles_o - 1 - i % a.qtiles_o;
-      prefill_single_own_item<DT, D>(a, lds, x + kXcds * (own % J), r, t);
+      prefill_single_own_item<DT, D, PLAN == kPrefillDirect>(a, lds, x + kXcds * (own % J), r, t);
     }
   } else {
     // prefix items of head 0, then of head 1 with the own items of head 0,
@@ -383,13 +400,18 @@ static hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t s, hipEvent
   const long items = (long)kXcds * ((a.H + kXcds - 1) / kXcds) * ((long)a.n_pre + a.n_own);
   const long blocks = items > a.meta_wgs ? items : a.meta_wgs;
   if (blocks <= 0) return hipSuccess;
+  const dim3 grid((unsigned)blocks), wg(256);
   if constexpr (DT != kF32) {
-    if (a.single) {
-      hipExtLaunchKernelGGL((k_prefill<DT, D, true>), dim3((unsigned)blocks), dim3(256), 0, s, e0, e1, 0, a);
+    if (a.plan == kPrefillStacked) {
+      hipExtLaunchKernelGGL((k_prefill<DT, D, kPrefillStacked>), grid, wg, 0, s, e0, e1, 0, a);
+      return hipGetLastError();
+    }
+    if (a.plan == kPrefillDirect) {
+      hipExtLaunchKernelGGL((k_prefill<DT, D, kPrefillDirect>), grid, wg, 0, s, e0, e1, 0, a);
       return hipGetLastError();
     }
   }
-  hipExtLaunchKernelGGL((k_prefill<DT, D, false>), dim3((unsigned)blocks), dim3(256), 0, s, e0, e1, 0, a);
+  hipExtLaunchKernelGGL((k_prefill<DT, D, kPrefillSplit>), grid, wg, 0, s, e0, e1, 0, a);
   return hipGetLastError();
 }
 
@@ -400,9 +422,12 @@ hipError_t launch_prefill(const PrefillArgs& a, int dtype, int D, hipStream_t s,
   if (a.cp % 32 != 0 || a.co % 32 != 0 || a.cp > kPrefillMaxBlocks * kBlock ||
       a.co > kPrefillMaxBlocks * kBlock || a.cp < 32 || a.co < 32)
     return hipErrorInvalidValue;
-  if (a.single && (dtype == kF32 || a.parents || a.depth != 1 || !a.out || !a.lse))
+  if (a.plan != kPrefillSplit && a.plan != kPrefillStacked && a.plan != kPrefillDirect)
     return hipErrorInvalidValue;
-  if (a.meta_wgs != (a.single ? 0 : (a.T + 255) / 256) || a.n_pre < 0 || a.n_own < 1 ||
+  if (a.plan != kPrefillSplit && (dtype == kF32 || a.parents || a.depth != 1 || !a.out || !a.lse))
+    return hipErrorInvalidValue;
+  if (a.plan == kPrefillDirect && a.n_pre != 0) return hipErrorInvalidValue;
+  if (a.meta_wgs != (a.plan != kPrefillSplit ? 0 : (a.T + 255) / 256) || a.n_pre < 0 || a.n_own < 1 ||
       (long)kXcds * ((a.H + kXcds - 1) / kXcds) * ((long)a.n_pre + a.n_own) > 0x7fffffffL)
     return hipErrorInvalidValue;
   switch (dtype * 1000 + D) {

@@ -9,8 +9,14 @@ namespace parrot {
 // q are request r's last Q_r own tokens.  Partial results use the decode
 // layout with rows in place of requests: o_part [T][H][seg][D], slots
 // [l*seg_p, (l+1)*seg_p) for prefix level l, [seg_pre, seg) for own-token
-// chunks of co tokens; merge_meta [T][4].  The single pass (single = 1)
-// writes out and lse itself and uses none of o_part, lse_part, merge_meta.
+// chunks of co tokens; merge_meta [T][4].  The single-pass plans write out and
+// lse themselves and use none of o_part, lse_part, merge_meta.
+enum PrefillPlanKind {
+  kPrefillSplit = 0,     // prefix and own items, partial results, merge
+  kPrefillStacked = 1,   // single pass: tiles of a group's stacked rows
+  kPrefillDirect = 2     // single pass: tiles of one request's rows, which read
+                         // its group's prefix themselves
+};
 struct PrefillArgs {
   const void* q;         // [T][H][D]
   const void* pk; const void* pv;
@@ -28,7 +34,7 @@ struct PrefillArgs {
   int n_pre, n_own;      // prefix-chunk and own-chunk work items per head
   int meta_wgs;          // workgroups that also write the row descriptors (256 rows each)
   float scale_log2;
-  int single;            // single-pass items (flat groups, one chunk each): write out, lse
+  int plan;              // PrefillPlanKind (single pass: flat groups, one chunk each)
   void* out; float* lse; // [T][H][D] dtype, [T][H] (single pass only)
 };
 
