@@ -105,7 +105,8 @@ typedef struct {
                             for prefill, the prefill kernel) */
   void* partials_stop;
   void* merge_start;     /* the log-sum-exp merge kernel (a prefill call on the single
-                            pass has none: both events are recorded back to back) */
+                            pass and a small decode call have none: both events are
+                            recorded back to back) */
   void* merge_stop;
 } parrot_trace;
 
@@ -131,6 +132,10 @@ size_t parrot_workspace_bytes(const parrot_problem* p);
  *        16-token blocks over a fixed grid, with 128-bit coalesced streaming
  *        loads; one partial per (request, head) piece;
  *   2. the merge kernel: log-sum-exp combination of all partials of (r, h).
+ * Small calls (few requests, short contexts; the same problem always decides
+ * the same way) run as one kernel instead: a workgroup per (request, head)
+ * attends to the whole context and writes the output, and the workspace stays
+ * unused.  This holds for every decode entry point below.
  *
  *   q                    [R][H][D] dtype, 16-byte aligned
  *   prefix_k, prefix_v   [num_prefix_blocks][H][B][D] dtype, 16-byte aligned

@@ -280,6 +280,43 @@ parrot_status launched(hipError_t e, const char* what) {
 
 #define PARROT_TRY(x) do { parrot_status _s = (x); if (_s != PARROT_OK) return _s; } while (0)
 
+// Waves per workgroup of the one-launch decode path (direct.hip), or 0 where the
+// partial-result and merge kernels are expected to be faster.  Both sides are
+// estimated in microseconds from the bounds in `p`, so every entry point makes
+// the same choice for the same problem; the figures are fits to sweeps on
+// MI355X (1-128 requests, prefixes of 0-2000 and own tokens of 20-3000, 5 to 32
+// heads, every dtype and head size):
+//  * two kernels: 9.3 us plus the bytes at 6.3 TB/s, each prefix read once (in
+//    fp32 the prefix role reaches 1.6 TB/s; on the per-request path every
+//    member's reads, at 17 TB/s from the caches);
+//  * one launch: 4.2 us, plus the longest context at 75 KB/us for its
+//    workgroup (rows under 512 bytes count as 512), or the own tokens at 5.4
+//    TB/s and every request's prefix reads at 17 TB/s from the L2 (6 where a
+//    head's workgroups do not share an XCD), plus 0.6 us per further workgroup
+//    of a CU.
+// Measured, two kernels / one, 32 heads: 8 requests of 300 tokens 12.5 / 9.1
+// us, 8 of 1000 24.2 / 22.5, 32 of 300 27.5 / 32.9; 8 on a 500-token prefix
+// 10.9 / 8.6, on a 2000-token one 14.7 / 18.6; 32 on a 500-token one 12.9 /
+// 19.3; five 64-wide heads, 40 requests on prefixes of 200-700: 10.8 / 12.4.
+int direct_waves(const parrot_problem* p, bool shared) {
+  const int depth = p->num_groups > 0 ? std::max(1, (int)p->max_prefix_depth) : 0;
+  const double pre = p->num_groups > 0 ? p->max_prefix_len : 0.0, own = p->max_suffix_len;
+  if (pre > parrot::kDirectMaxTokens || own > parrot::kDirectMaxTokens) return 0;
+  const bool f32 = p->dtype == PARROT_DTYPE_F32;
+  const double R = p->num_requests, H = p->num_heads, cus = num_cus();
+  const double row = 2.0 * p->head_dim * (f32 ? 4.0 : 2.0);   // K and V of one token and head
+  const double own_bytes = R * own * H * row, member_bytes = R * depth * pre * H * row;
+  const double two = 9.3 + own_bytes / 6.3e6 +
+                     (shared ? p->num_groups * pre * H * row / (f32 ? 1.6e6 : 6.3e6) : member_bytes / 17e6);
+  const double wgs = R * H;
+  const double one = 4.2 +
+                     std::max((depth * pre + own) * std::max(row, 512.0) / 75e3,
+                              own_bytes / 5.4e6 + member_bytes / (p->num_heads % 8 == 0 ? 17e6 : 6e6)) +
+                     0.6 * std::max(0.0, wgs / cus - 1.0);
+  if (wgs > 2e9 || one > 0.95 * two) return 0;
+  return wgs <= cus ? 8 : 4;
+}
+
 // shared: prefix-group role for the prefixes (else the split-KV role reads
 // them per request); parents: nested groups (shared path only; NULL = flat).
 // k_new / v_new (both or neither): append this step's token to the suffix
@@ -357,6 +394,16 @@ parrot_status decode(bool shared, const parrot_problem* p, const void* q, const 
     a.nwaves = pa.n_skv * parrot::kSkvWaves;
     a.min_q = pl.skv_min_q;
     a.scale_log2 = scale_log2;
+    if (const int waves = direct_waves(p, shared)) {
+      PARROT_TRY(launched(parrot::launch_direct(a, out, lse, waves, dt, D, s, ev(tr.partials_start),
+                                                ev(tr.partials_stop)),
+                          "decode kernel"));
+      // no merge: its trace events, if asked for, bracket nothing
+      if (tr.merge_start) PARROT_TRY(hip_ok(hipEventRecord(ev(tr.merge_start), s), "hipEventRecord"));
+      if (tr.merge_stop) PARROT_TRY(hip_ok(hipEventRecord(ev(tr.merge_stop), s), "hipEventRecord"));
+      g_err.clear();
+      return PARROT_OK;
+    }
     if (run_prefix) {
       parrot::PrefixArgs& b = pa.pre;
       b.q = q; b.pk = prefix_k; b.pv = prefix_v; b.ptab = ptab; b.plen = plen; b.gid = gid;

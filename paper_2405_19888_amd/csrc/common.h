@@ -118,6 +118,11 @@ struct PartialsArgs {
 hipError_t launch_partials(const PartialsArgs& a, int dtype, int D, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_merge(const MergeArgs& a, int dtype, int D, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_validate(const ValidateArgs& a, hipStream_t s);
+// one launch for a whole small call (out and lse written directly); uses none of
+// the partial-result fields
+constexpr int kDirectMaxTokens = 4096;   // per prefix level and of own tokens
+hipError_t launch_direct(const SplitKVArgs& a, void* out, float* lse, int waves, int dtype, int D,
+                         hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 
 // ------------------------------------------------------------ device helpers
 #if defined(__HIP_DEVICE_COMPILE__)
