@@ -316,7 +316,9 @@ parrot_status parrot_validate_nested_inputs(
  * keys.
  *
  * Rows are computed in tiles of 128 (fp16 / bf16 caches) or 64 (fp32) on
- * MFMA, with K/V staged in LDS.  Two kinds of plan, chosen per call:
+ * MFMA, with K/V staged in LDS; calls with very few rows run without tiles, one
+ * workgroup per (row, head) that reads the row's whole context and writes its
+ * output (any dtype, nested groups too).  For the others two kinds of plan:
  *   single pass (flat groups, 16-bit caches, prefix and own lengths of at most
  *     8192 tokens): one kernel that writes the output directly and leaves the
  *     workspace unused.  Either a tile of the rows of a group's members (all
@@ -329,12 +331,13 @@ parrot_status parrot_validate_nested_inputs(
  *     items (one request's rows against one chunk of its own tokens, per-row
  *     causal limit) write partial results to the workspace, then the merge
  *     kernel combines them per (row, head).
- * The single pass is taken where an estimate from the sizes in `p` and `rows`
- * expects it to be faster; parrot_prefill_single_pass tells which one a call
- * takes.  The environment variable PARROT_PREFILL_SINGLE_PASS=0 forces the
+ * The split plan is left where an estimate from the sizes in `p` and `rows`
+ * expects another to be faster; parrot_prefill_single_pass tells whether a call
+ * writes its output directly.  The environment variable PARROT_PREFILL_SINGLE_PASS=0 forces the
  * split plan; =1 takes the single pass of stacked rows and =2 that of one
  * request per tile wherever the groups are flat, the caches 16-bit and the
- * lengths at most 8192; other values leave the choice to the estimate.  All
+ * lengths at most 8192, =3 the one without tiles wherever no prefix or own
+ * length exceeds 4096; other values leave the choice to the estimate.  All
  * plans give the same results to rounding.
  *
  *   rows                 (host) row counts; see parrot_prefill_rows
@@ -362,10 +365,11 @@ typedef struct {
  * parrot_workspace_bytes.  (size_t)-1 if the arguments are invalid. */
 size_t parrot_prefill_workspace_bytes(const parrot_problem* p, const parrot_prefill_rows* rows);
 
-/* 1 when parrot_shared_prefix_prefill takes the single pass for these
- * arguments on the current device, 0 when it takes the split plan, -1 if the
- * arguments are invalid.  `nested` is nonzero when prefix_parents will be
- * non-NULL (nested groups always take the split plan). */
+/* 1 when parrot_shared_prefix_prefill takes a single pass (or, with very few
+ * rows, no tiles) for these arguments on the current device, 0 when it takes
+ * the split plan, -1 if the arguments are invalid.  `nested` is nonzero when
+ * prefix_parents will be non-NULL (nested groups never take the tiled single
+ * pass). */
 int parrot_prefill_single_pass(const parrot_problem* p, const parrot_prefill_rows* rows, int nested);
 
 parrot_status parrot_shared_prefix_prefill(

@@ -278,6 +278,16 @@ parrot_status launched(hipError_t e, const char* what) {
   return PARROT_OK;
 }
 
+// End of a call whose single kernel wrote the output: the merge's trace events,
+// if asked for, bracket nothing.
+parrot_status no_merge(const parrot_trace& tr, hipStream_t s) {
+  parrot_status st = PARROT_OK;
+  if (tr.merge_start) st = hip_ok(hipEventRecord(ev(tr.merge_start), s), "hipEventRecord");
+  if (st == PARROT_OK && tr.merge_stop) st = hip_ok(hipEventRecord(ev(tr.merge_stop), s), "hipEventRecord");
+  if (st == PARROT_OK) g_err.clear();
+  return st;
+}
+
 #define PARROT_TRY(x) do { parrot_status _s = (x); if (_s != PARROT_OK) return _s; } while (0)
 
 // Waves per workgroup of the one-launch decode path (direct.hip), or 0 where the
@@ -371,6 +381,25 @@ parrot_status decode(bool shared, const parrot_problem* p, const void* q, const 
   const float scale_log2 = p->sm_scale * parrot::kLog2e;
   const int D = p->head_dim, dt = (int)p->dtype;
 
+  if (const int waves = direct_waves(p, shared)) {
+    parrot::DirectArgs a{};
+    a.q = q; a.pk = prefix_k; a.pv = prefix_v; a.sk = suffix_k; a.sv = suffix_v;
+    a.ptab = ptab; a.plen = plen; a.stab = stab; a.slen = slen; a.gid = gid;
+    a.parents = parents;
+    a.depth = parents ? pl.depth : 1;
+    a.k_new = k_new; a.v_new = v_new;
+    a.app_k = const_cast<void*>(suffix_k); a.app_v = const_cast<void*>(suffix_v);
+    a.out = out; a.lse = lse;
+    a.R = p->num_requests; a.H = p->num_heads; a.NG = p->num_groups;
+    a.pstride = p->prefix_table_stride; a.sstride = p->suffix_table_stride;
+    a.max_p = p->max_prefix_len; a.max_s = p->max_suffix_len;
+    a.npblk = p->num_groups > 0 ? p->num_prefix_blocks : 1; a.nsblk = p->num_suffix_blocks;
+    a.scale_log2 = scale_log2;
+    PARROT_TRY(launched(parrot::launch_direct(a, waves, dt, D, s, ev(tr.partials_start), ev(tr.partials_stop)),
+                        "decode kernel"));
+    return no_merge(tr, s);
+  }
+
   const bool run_prefix = shared && p->num_groups > 0 && pl.seg_p > 0;
   {
     parrot::PartialsArgs pa{};
@@ -394,16 +423,6 @@ parrot_status decode(bool shared, const parrot_problem* p, const void* q, const 
     a.nwaves = pa.n_skv * parrot::kSkvWaves;
     a.min_q = pl.skv_min_q;
     a.scale_log2 = scale_log2;
-    if (const int waves = direct_waves(p, shared)) {
-      PARROT_TRY(launched(parrot::launch_direct(a, out, lse, waves, dt, D, s, ev(tr.partials_start),
-                                                ev(tr.partials_stop)),
-                          "decode kernel"));
-      // no merge: its trace events, if asked for, bracket nothing
-      if (tr.merge_start) PARROT_TRY(hip_ok(hipEventRecord(ev(tr.merge_start), s), "hipEventRecord"));
-      if (tr.merge_stop) PARROT_TRY(hip_ok(hipEventRecord(ev(tr.merge_stop), s), "hipEventRecord"));
-      g_err.clear();
-      return PARROT_OK;
-    }
     if (run_prefix) {
       parrot::PrefixArgs& b = pa.pre;
       b.q = q; b.pk = prefix_k; b.pv = prefix_v; b.ptab = ptab; b.plen = plen; b.gid = gid;
@@ -600,18 +619,19 @@ constexpr int kPrefillChunkMin = 256;
 struct PrefillPlan {
   int depth, cp, co, seg_p, seg_pre, seg_s, seg, qtiles_p, qtiles_o;
   long n_pre, n_own;
+  int waves;     // kPrefillRows: waves per workgroup
   int kind;      // PrefillPlanKind; the single-pass kinds have no partial results and no merge
   size_t o_bytes, lse_bytes, info_bytes, total_bytes;
 };
 
 // PARROT_PREFILL_SINGLE_PASS=0 turns the single-pass plans off; =1 takes the
 // stacked one and =2 the per-request one wherever the groups are flat, the
-// caches 16-bit and the ranges fit the tile's block table (8192 tokens), for
-// tests and tuning.  Any other value (or none) leaves the choice to the cost
+// caches 16-bit and the ranges fit the tile's block table (8192 tokens), =3 the
+// one without tiles wherever no range exceeds 4096, for tests and tuning.  Any other value (or none) leaves the choice to the cost
 // estimate below.
 int single_pass_setting() {
   const char* e = std::getenv("PARROT_PREFILL_SINGLE_PASS");
-  if (e && e[0] >= '0' && e[0] <= '2' && e[1] == 0) return e[0] - '0';
+  if (e && e[0] >= '0' && e[0] <= '3' && e[1] == 0) return e[0] - '0';
   return -1;
 }
 
@@ -688,6 +708,28 @@ PrefillCosts prefill_costs(const parrot_problem* p, const parrot_prefill_rows* r
   return c;
 }
 
+// Estimated microseconds of a prefill without tiles (direct.hip: one workgroup
+// per row and head that reads the row's whole context), or -1 where it is not
+// built: as for the one-launch decode, plus the round trip that finds the row's
+// request and 0.9 us per further workgroup of a CU; repeated reads come from the caches at 22 TB/s (8 where a head's
+// workgroups spread over more than two XCDs).  The tiles' estimates run high
+// where everything waits on round trips (13.6 us measured for 21 estimated) and
+// low for the fp32 tile (18 and 33 us for 14 and 21), hence the factors at the
+// call.  Measured, tiles / rows: 4 fp32 requests of 16-32 rows on a 128-token
+// prefix, 4 heads 18.5 / 6.3 us; one fp16 request of 8-16 rows on 600 tokens, 4
+// heads 14.3 / 8.1; 16 of 1-4 rows on 100 tokens, 4 heads 9.3 / 5.4, 32 heads
+// 10.4 / 11.3; 4 of 8-16 rows on 100, 32 heads 9.5 / 11.7.
+double direct_rows_cost(const parrot_problem* p, long T, int depth) {
+  const double pre = p->num_groups > 0 ? p->max_prefix_len : 0.0, own = p->max_suffix_len;
+  if (pre > parrot::kDirectMaxTokens || own > parrot::kDirectMaxTokens) return -1.0;
+  const double row = 2.0 * p->head_dim * (p->dtype == PARROT_DTYPE_F32 ? 4.0 : 2.0);
+  const double wgs = (double)T * p->num_heads, tokens = depth * pre + own;
+  return 4.6 +
+         std::max(tokens * std::max(row, 512.0) / 75e3,
+                  wgs * tokens * row / (p->num_heads % 4 == 0 || p->num_heads <= 2 ? 22e6 : 8e6)) +
+         0.9 * std::max(0.0, wgs / num_cus() - 1.0);
+}
+
 parrot_status check_prefill(const parrot_problem* p, const parrot_prefill_rows* rows, bool nested,
                             PrefillPlan* pl) {
   if (!p) return fail(PARROT_ERR_INVALID_ARGUMENT, "problem is NULL");
@@ -739,14 +781,21 @@ parrot_status check_prefill(const parrot_problem* p, const parrot_prefill_rows* 
   const int setting = single_pass_setting();
   const bool fits = p->max_prefix_len <= kPrefillChunkMax && p->max_suffix_len <= kPrefillChunkMax;
   const bool can = p->dtype != PARROT_DTYPE_F32 && !nested && fits;
-  if (can && setting >= 1) {
+  if (can && (setting == 1 || setting == 2)) {
     pl->kind = setting;
-  } else if (can && setting == -1) {
-    // the single-pass plans where they are expected to be clearly faster
+  } else if (setting == -1 || setting == 3) {
+    // the tiled single-pass plans where they are expected to be clearly faster
     const PrefillCosts c = prefill_costs(p, rows, *pl);
-    const double best = std::min(c.stacked, c.direct);
-    if (best < 0.9 * c.split)
+    double best = c.split;
+    if (can && setting == -1 && std::min(c.stacked, c.direct) < 0.9 * c.split) {
+      best = std::min(c.stacked, c.direct);
       pl->kind = c.direct < c.stacked ? parrot::kPrefillDirect : parrot::kPrefillStacked;
+    }
+    const double one = direct_rows_cost(p, T, pl->depth);
+    if (one >= 0.0 && (setting == 3 || one < (p->dtype == PARROT_DTYPE_F32 ? 1.2 : 0.6) * best)) {
+      pl->kind = parrot::kPrefillRows;
+      pl->waves = (double)T * H <= num_cus() ? 8 : 4;
+    }
   }
   if (pl->kind != parrot::kPrefillSplit) {   // one item per group tile (whole prefix), one per own tile
     pl->n_pre = pl->kind == parrot::kPrefillStacked && pl->seg_p > 0 ? (long)p->num_groups * pl->qtiles_p : 0;
@@ -805,6 +854,23 @@ parrot_status prefill(const parrot_problem* p, const parrot_prefill_rows* rows, 
   float* lse_part = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + pl.o_bytes);
   int* merge_meta = reinterpret_cast<int*>(reinterpret_cast<char*>(workspace) + pl.o_bytes + pl.lse_bytes);
   const int T = rows->num_query_rows;
+  if (pl.kind == parrot::kPrefillRows) {
+    parrot::DirectArgs a{};
+    a.q = q; a.pk = prefix_k; a.pv = prefix_v; a.sk = suffix_k; a.sv = suffix_v;
+    a.ptab = ptab; a.plen = plen; a.stab = stab; a.slen = slen; a.gid = gid;
+    a.parents = p->num_groups > 0 ? parents : nullptr; a.qoff = qoff;
+    a.depth = std::max(1, pl.depth);
+    a.out = out; a.lse = lse;
+    a.R = p->num_requests; a.H = p->num_heads; a.NG = p->num_groups; a.T = T; a.max_q = rows->max_query_rows;
+    a.pstride = p->prefix_table_stride; a.sstride = p->suffix_table_stride;
+    a.max_p = p->max_prefix_len; a.max_s = p->max_suffix_len;
+    a.npblk = p->num_groups > 0 ? p->num_prefix_blocks : 1; a.nsblk = p->num_suffix_blocks;
+    a.scale_log2 = p->sm_scale * parrot::kLog2e;
+    PARROT_TRY(launched(parrot::launch_direct(a, pl.waves, (int)p->dtype, p->head_dim, s, ev(tr.partials_start),
+                                              ev(tr.partials_stop)),
+                        "prefill kernel"));
+    return no_merge(tr, s);
+  }
   {
     parrot::PrefillArgs a{};
     a.q = q; a.pk = prefix_k; a.pv = prefix_v; a.sk = suffix_k; a.sv = suffix_v;
@@ -827,11 +893,8 @@ parrot_status prefill(const parrot_problem* p, const parrot_prefill_rows* rows, 
                                                ev(tr.partials_stop)),
                         "prefill kernel"));
   }
-  if (pl.kind != parrot::kPrefillSplit) {
-    // no merge: its trace events, if asked for, bracket nothing
-    if (tr.merge_start) PARROT_TRY(hip_ok(hipEventRecord(ev(tr.merge_start), s), "hipEventRecord"));
-    if (tr.merge_stop) PARROT_TRY(hip_ok(hipEventRecord(ev(tr.merge_stop), s), "hipEventRecord"));
-  } else {
+  if (pl.kind != parrot::kPrefillSplit) return no_merge(tr, s);
+  {
     parrot::MergeArgs a{};
     a.o_part = o_part; a.lse_part = lse_part; a.merge_meta = merge_meta;
     a.out = out; a.lse = lse;

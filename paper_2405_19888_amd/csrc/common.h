@@ -118,11 +118,31 @@ struct PartialsArgs {
 hipError_t launch_partials(const PartialsArgs& a, int dtype, int D, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_merge(const MergeArgs& a, int dtype, int D, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_validate(const ValidateArgs& a, hipStream_t s);
-// one launch for a whole small call (out and lse written directly); uses none of
-// the partial-result fields
+// One launch for a whole small call (direct.hip): decode of R requests, or with
+// qoff prefill of T rows (query_offsets; max_q bounds a request's rows).
+struct DirectArgs {
+  const void* q;
+  const void* pk; const void* pv;
+  const void* sk; const void* sv;
+  const int* ptab; const int* plen;
+  const int* stab; const int* slen;
+  const int* gid;
+  const int* parents;    // nested groups (NULL: flat)
+  const int* qoff;       // prefill row offsets [R + 1] (NULL: decode)
+  const void* k_new;     // this step's token per (request, head), or NULL
+  const void* v_new;
+  void* app_k; void* app_v;   // pools the new token is written to (suffix pools)
+  void* out; float* lse;
+  int R, H, NG, T, max_q;
+  int pstride, sstride;
+  int max_p, max_s;
+  int npblk, nsblk;
+  int depth;             // prefix levels walked
+  float scale_log2;
+};
 constexpr int kDirectMaxTokens = 4096;   // per prefix level and of own tokens
-hipError_t launch_direct(const SplitKVArgs& a, void* out, float* lse, int waves, int dtype, int D,
-                         hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+hipError_t launch_direct(const DirectArgs& a, int waves, int dtype, int D, hipStream_t s, hipEvent_t e0,
+                         hipEvent_t e1);
 
 // ------------------------------------------------------------ device helpers
 #if defined(__HIP_DEVICE_COMPILE__)

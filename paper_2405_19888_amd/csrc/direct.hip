@@ -1,5 +1,6 @@
-// Decode of small calls in one launch: one workgroup per (request, head)
-// attends to the request's whole context and writes its output.
+// Small calls in one launch: one workgroup per (request, head) attends to the
+// request's whole context and writes its output (decode), or one per (new row,
+// head) of a prefill with few rows.
 //
 // The two-kernel path (partial results, merge) costs a small call two launches
 // and about seven dependent memory round trips: lengths, scan, block table,
@@ -23,10 +24,15 @@
 
 namespace parrot {
 
-// NW: waves per workgroup
-template <int DT, int D, bool APPEND, int NW>
-__global__ __launch_bounds__(NW * 64) void k_direct(SplitKVArgs a, void* out, float* lse) {
+enum DirectMode { kDirectPlain = 0, kDirectAppend = 1, kDirectRows = 2 };
+
+// NW: waves per workgroup.  MODE: plain decode, decode that appends this step's
+// token, or prefill rows (a.qoff, a.T and a.max_q: workgroup (row, head), the
+// row's request sees its prefixes and its own tokens up to the row's position).
+template <int DT, int D, int MODE, int NW>
+__global__ __launch_bounds__(NW * 64) void k_direct(DirectArgs a) {
   using E = Elem<DT>;
+  constexpr bool APPEND = MODE == kDirectAppend;
   constexpr int ROW_B = D * E::kBytes;        // bytes per token row
   constexpr int LPT = ROW_B / 16;             // lanes per token
   constexpr int TPI = kWave / LPT;            // tokens per load instruction
@@ -40,7 +46,8 @@ __global__ __launch_bounds__(NW * 64) void k_direct(SplitKVArgs a, void* out, fl
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int H = a.H;
   const int h = blockIdx.x % H;
-  const int r = blockIdx.x / H;
+  const int x = blockIdx.x / H;               // request, or prefill row
+  int r = x;
   const int sub = lane % LPT;                 // which 16-byte slice of the row
   const int tg = lane / LPT;                  // token group
   const size_t blk_stride = (size_t)H * BLK_B;
@@ -48,12 +55,36 @@ __global__ __launch_bounds__(NW * 64) void k_direct(SplitKVArgs a, void* out, fl
   // one round of loads: the query, the lengths and the own table's entries.
   // Wave w takes blocks w, w + NW, ... of each list; lane k holds the entry of
   // its k-th (the host keeps every list within 64 NW blocks).
-  const u32x4 q = ld16((const char*)a.q + ((size_t)(r * H + h) * D + sub * EPL) * E::kBytes);
+  const u32x4 q = ld16((const char*)a.q + ((size_t)(x * H + h) * D + sub * EPL) * E::kBytes);
   const int col = w + NW * lane;
+  int first = 0, count = 0;
+  if constexpr (MODE == kDirectRows) {
+    // the row's request: the last one whose first row is at or before it
+    r = -1;
+    for (int base = 0; base < a.R; base += kWave) {
+      const int rr = base + lane;
+      const unsigned long long mask = __ballot(rr < a.R && a.qoff[min(rr, a.R - 1)] <= x);
+      if (mask != 0) r = base + 63 - __builtin_clzll(mask);
+      if (mask != ~0ull) break;
+    }
+    first = r >= 0 ? clampi(a.qoff[r], 0, a.T) : 0;
+    const long n = r >= 0 ? (long)a.qoff[r + 1] - a.qoff[r] : 0;
+    count = (int)(n < 0 ? 0 : n > a.max_q ? a.max_q : n);
+    r = r < 0 ? 0 : r;
+  }
   int e_own = 0;
   if (a.sstride > 0) e_own = a.stab[(long)r * a.sstride + min(col, a.sstride - 1)];
-  const int S = clampi(a.slen[r], 0, a.max_s);
+  int S = clampi(a.slen[r], 0, a.max_s);
   int g = a.gid[r];
+  if constexpr (MODE == kDirectRows) {
+    // own tokens up to the row's position; a row that no request holds (as
+    // when a request has more rows than the bounds allow) sees nothing
+    count = min(count, min(S, a.T - first));
+    const int pos = S - count + (x - first);
+    const bool held = x >= first && x < first + count;
+    S = held ? pos + 1 : 0;
+    g = held ? g : -1;
+  }
   const int nbs = (S + kBlock - 1) / kBlock;
 
   // the prefixes of the request's chain of groups, innermost first
@@ -231,44 +262,45 @@ __global__ __launch_bounds__(NW * 64) void k_direct(SplitKVArgs a, void* out, fl
     o = __builtin_fmaf(c, s_acc[i][d], o);
   }
   // an empty context is defined as out = 0, lse = -inf
-  E::store1((char*)out + ((size_t)(r * H + h) * D + d) * E::kBytes, tot > 0.f ? o / tot : 0.f);
-  if (d == 0) lse[r * H + h] = tot > 0.f ? (mx + fast_log2(tot)) * kLn2 : -INFINITY;
+  E::store1((char*)a.out + ((size_t)(x * H + h) * D + d) * E::kBytes, tot > 0.f ? o / tot : 0.f);
+  if (d == 0) a.lse[x * H + h] = tot > 0.f ? (mx + fast_log2(tot)) * kLn2 : -INFINITY;
 }
 
 template <int DT, int D, int NW>
-static void launch_direct_nw(const SplitKVArgs& a, void* out, float* lse, hipStream_t s, hipEvent_t e0,
-                             hipEvent_t e1) {
-  const dim3 grid((unsigned)(a.R * a.H)), wg(NW * 64);
-  if (a.k_new)
-    hipExtLaunchKernelGGL((k_direct<DT, D, true, NW>), grid, wg, 0, s, e0, e1, 0, a, out, lse);
+static void launch_direct_nw(const DirectArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 grid((unsigned)((a.qoff ? a.T : a.R) * a.H)), wg(NW * 64);
+  if (a.qoff)
+    hipExtLaunchKernelGGL((k_direct<DT, D, kDirectRows, NW>), grid, wg, 0, s, e0, e1, 0, a);
+  else if (a.k_new)
+    hipExtLaunchKernelGGL((k_direct<DT, D, kDirectAppend, NW>), grid, wg, 0, s, e0, e1, 0, a);
   else
-    hipExtLaunchKernelGGL((k_direct<DT, D, false, NW>), grid, wg, 0, s, e0, e1, 0, a, out, lse);
+    hipExtLaunchKernelGGL((k_direct<DT, D, kDirectPlain, NW>), grid, wg, 0, s, e0, e1, 0, a);
 }
 
 template <int DT, int D>
-static hipError_t launch_direct_t(const SplitKVArgs& a, void* out, float* lse, int waves, hipStream_t s,
-                                  hipEvent_t e0, hipEvent_t e1) {
+static hipError_t launch_direct_t(const DirectArgs& a, int waves, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (waves == 8)
-    launch_direct_nw<DT, D, 8>(a, out, lse, s, e0, e1);
+    launch_direct_nw<DT, D, 8>(a, s, e0, e1);
   else
-    launch_direct_nw<DT, D, 4>(a, out, lse, s, e0, e1);
+    launch_direct_nw<DT, D, 4>(a, s, e0, e1);
   return hipGetLastError();
 }
 
-hipError_t launch_direct(const SplitKVArgs& a, void* out, float* lse, int waves, int dtype, int D,
-                         hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+hipError_t launch_direct(const DirectArgs& a, int waves, int dtype, int D, hipStream_t s, hipEvent_t e0,
+                         hipEvent_t e1) {
   // a lane holds one table entry per list: at most 64 blocks per wave and list
   const int most = waves * kWave * kBlock;
-  if (a.R < 1 || a.H < 1 || (long)a.R * a.H > 0x7fffffffL || a.depth > kMaxDepth ||
-      (waves != 4 && waves != 8) || a.max_s > most || (a.NG > 0 && a.max_p > most))
+  const long groups = (long)(a.qoff ? a.T : a.R) * a.H;
+  if (a.R < 1 || a.H < 1 || groups < 1 || groups > 0x7fffffffL || a.depth > kMaxDepth ||
+      (waves != 4 && waves != 8) || a.max_s > most || (a.NG > 0 && a.max_p > most) || (a.qoff && a.k_new))
     return hipErrorInvalidValue;
   switch (dtype * 1000 + D) {
-    case kF32 * 1000 + 64: return launch_direct_t<kF32, 64>(a, out, lse, waves, s, e0, e1);
-    case kF32 * 1000 + 128: return launch_direct_t<kF32, 128>(a, out, lse, waves, s, e0, e1);
-    case kF16 * 1000 + 64: return launch_direct_t<kF16, 64>(a, out, lse, waves, s, e0, e1);
-    case kF16 * 1000 + 128: return launch_direct_t<kF16, 128>(a, out, lse, waves, s, e0, e1);
-    case kBF16 * 1000 + 64: return launch_direct_t<kBF16, 64>(a, out, lse, waves, s, e0, e1);
-    case kBF16 * 1000 + 128: return launch_direct_t<kBF16, 128>(a, out, lse, waves, s, e0, e1);
+    case kF32 * 1000 + 64: return launch_direct_t<kF32, 64>(a, waves, s, e0, e1);
+    case kF32 * 1000 + 128: return launch_direct_t<kF32, 128>(a, waves, s, e0, e1);
+    case kF16 * 1000 + 64: return launch_direct_t<kF16, 64>(a, waves, s, e0, e1);
+    case kF16 * 1000 + 128: return launch_direct_t<kF16, 128>(a, waves, s, e0, e1);
+    case kBF16 * 1000 + 64: return launch_direct_t<kBF16, 64>(a, waves, s, e0, e1);
+    case kBF16 * 1000 + 128: return launch_direct_t<kBF16, 128>(a, waves, s, e0, e1);
   }
   return hipErrorInvalidValue;
 }

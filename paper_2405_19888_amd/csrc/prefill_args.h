@@ -14,8 +14,10 @@ namespace parrot {
 enum PrefillPlanKind {
   kPrefillSplit = 0,     // prefix and own items, partial results, merge
   kPrefillStacked = 1,   // single pass: tiles of a group's stacked rows
-  kPrefillDirect = 2     // single pass: tiles of one request's rows, which read
+  kPrefillDirect = 2,    // single pass: tiles of one request's rows, which read
                          // its group's prefix themselves
+  kPrefillRows = 3       // single pass without tiles: one workgroup per (row, head)
+                         // (direct.hip), for calls with few rows
 };
 struct PrefillArgs {
   const void* q;         // [T][H][D]
