@@ -435,15 +435,16 @@ parrot_status decode(bool shared, const parrot_problem* p, const void* q, const 
       b.scale_log2 = scale_log2;
       pa.n_pre = p->num_groups * pl.seg_p * p->num_heads * pl.prefix_qtiles;
     }
-    // The split-KV role holds its per-request scan in LDS for up to
-    // kMaxRequests requests, so a larger batch is streamed in slices of that
-    // many requests, one launch each (every per-request pointer moved to the
+    // The split-KV role holds its per-request scan in LDS for up to 4096
+    // requests (1024 on the per-request path), so a larger batch is streamed in
+    // slices of that many requests, one launch each (every per-request pointer moved to the
     // slice); the prefix-group role covers every request in the first launch,
     // and one merge follows.  The trace brackets all of them.
     const int R = p->num_requests, H = p->num_heads;
     const size_t elt = p->dtype == PARROT_DTYPE_F32 ? 4 : 2;
-    for (int r0 = 0; r0 < R; r0 += parrot::kMaxRequests) {
-      const int rn = std::min(parrot::kMaxRequests, R - r0);
+    const int most = shared ? parrot::kMaxRequests : parrot::kMaxRequestsPrefix;
+    for (int r0 = 0; r0 < R; r0 += most) {
+      const int rn = std::min(most, R - r0);
       parrot::PartialsArgs slice = pa;
       parrot::SplitKVArgs& c = slice.skv;
       const size_t rows = (size_t)r0 * H;

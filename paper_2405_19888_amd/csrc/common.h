@@ -38,7 +38,10 @@ struct Plan {
   size_t o_bytes, lse_bytes, info_bytes, total_bytes;
 };
 
-constexpr int kMaxRequests = 1024;   // per call (split-KV keeps per-request data in LDS)
+// requests per launch (split-KV keeps per-request data in LDS): shared path, and
+// per-request path (more data per request)
+constexpr int kMaxRequests = 4096;
+constexpr int kMaxRequestsPrefix = 1024;
 constexpr int kSkvWaves = 4;         // waves per split-KV workgroup
 constexpr int kMaxDepth = 4;         // prefix levels of nested groups
 constexpr int kMetaInts = 4;         // merge_meta ints per request

@@ -72,7 +72,7 @@ static hipError_t launch_partials_t(const PartialsArgs& a, hipStream_t s, hipEve
 
 hipError_t launch_partials(const PartialsArgs& a, int dtype, int D, hipStream_t s, hipEvent_t e0,
                            hipEvent_t e1) {
-  if (a.skv.R > kMaxRequests || a.n_skv < 1 || a.skv.nwaves != a.n_skv * kSkvWaves ||
+  if (a.skv.R > (a.skv.with_prefix ? kMaxRequestsPrefix : kMaxRequests) || a.n_skv < 1 || a.skv.nwaves != a.n_skv * kSkvWaves ||
       (a.skv.hpw != 1 && a.skv.hpw != 2) || a.skv.H % a.skv.hpw != 0 ||
       (a.skv.hpw == 2 && (a.skv.with_prefix || dtype == kF32)) ||
       a.skv.nwaves / (a.skv.H / a.skv.hpw) < 1)

@@ -41,6 +41,8 @@ constexpr int kStageBytes = 2 * kTensorStage;
 constexpr int kStageChunks = kStageBytes / 1024;  // 1 KiB per direct-to-LDS instruction
 constexpr int kRing = 3;             // stage buffers in LDS (kRing - 1 stages in flight)
 constexpr int kMaxChunkBlocks = 64;  // prefix chunk <= 1024 tokens
+constexpr int kMemberSteps = 8;      // member scan: 64-request steps per wave and round
+constexpr int kMemberFew = 256;      // requests that one wave tests alone
 
 
 typedef __attribute__((address_space(3))) char lds_char;
@@ -139,7 +141,7 @@ struct TileLds {
   char (*smem)[prefix_detail::kStageBytes];   // [ring][kStageBytes]
   int* rows;                                  // [rows] query row of each tile column
   int* tbl;                                   // [blocks] key blocks, clamped
-  int* count;                                 // set-up scratch
+  int* count;                                 // [4] set-up scratch
   int* lim;                                   // [rows] last visible key token (causal)
   PARROT_DEV explicit TileLds(char* lds, int blocks = prefix_detail::kMaxChunkBlocks,
                               int nrows = kPrefixWaves * 16, int ring = prefix_detail::kRing)
@@ -179,7 +181,6 @@ __device__ __forceinline__ void prefix_role(const PrefixArgs& a, char* lds, int 
   const TileLds tl(lds, kMaxChunkBlocks, W * 16, kDecodeRing);
   int* members = tl.rows;
   int* s_tbl = tl.tbl;
-  int& s_count = tl.count[0];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -209,32 +210,88 @@ __device__ __forceinline__ void prefix_role(const PrefixArgs& a, char* lds, int 
   const int nb = (t1 - t0 + kBlock - 1) / kBlock;     // <= cp / 16 <= kMaxChunkBlocks
   const int* tbl = a.ptab + (long)g * a.pstride;
 
-  // members of group g in request order (this tile takes [qbase, qbase + 16 W));
-  // the chunk's block ids, clamped into the pool
-  if (wave == 0) {
-    int count = 0;
-    for (int base = 0; base < a.R; base += kWave) {
-      const int r = base + lane;
-      // r reads g's prefix when g is r's group or one of its ancestors
-      bool is = false;
-      if (r < a.R) {
-        int x = a.gid[r];
-        for (int d = 0; d < a.depth && x >= 0 && x < a.NG; ++d) {
-          if (x == g) { is = true; break; }
-          x = a.parents ? a.parents[x] : -1;
+  // Members of group g in request order (this tile takes [qbase, qbase + 16 W)),
+  // and the chunk's block ids, clamped into the pool.  A request reads g's prefix
+  // when g is its group or one of its ancestors.
+  auto reads = [&](int r, int x) {
+    if (r >= a.R) return false;
+    for (int d = 0; d < a.depth && x >= 0 && x < a.NG; ++d) {
+      if (x == g) return true;
+      x = a.parents ? a.parents[x] : -1;
+    }
+    return false;
+  };
+  static_assert(kMaxChunkBlocks <= kWave, "one block id per lane");
+  int total = 0;
+  if (a.R <= kMemberFew) {
+    // few requests: wave 0 tests them all, wave 1 reads the table, one barrier
+    if (wave == 0) {
+      int x[kMemberFew / kWave];
+#pragma unroll
+      for (int i = 0; i < kMemberFew / kWave; ++i)
+        x[i] = i * kWave < a.R ? a.gid[min(i * kWave + lane, a.R - 1)] : -1;
+#pragma unroll
+      for (int i = 0; i < kMemberFew / kWave; ++i) {
+        if (i * kWave < a.R) {
+          const bool is = reads(i * kWave + lane, x[i]);
+          const unsigned long long mask = __ballot(is);
+          const int pos = total + __popcll(mask & ((1ull << lane) - 1ull));
+          if (is && pos >= qbase && pos < qbase + W * 16) members[pos - qbase] = i * kWave + lane;
+          total += __popcll(mask);
         }
       }
-      const unsigned long long mask = __ballot(is);
-      const int pos = count + __popcll(mask & ((1ull << lane) - 1ull));
-      if (is && pos >= qbase && pos < qbase + W * 16) members[pos - qbase] = r;
-      count += __popcll(mask);
+      if (lane == 0) tl.count[0] = total;
+    } else if (wave == 1) {
+      if (lane < nb) s_tbl[lane] = clampi(tbl[b0 + lane], 0, a.npblk - 1);
     }
-    if (lane == 0) s_count = count;
-  } else if (wave == 1) {
-    for (int i = lane; i < nb; i += kWave) s_tbl[i] = clampi(tbl[b0 + i], 0, a.npblk - 1);
+    __syncthreads();
+    total = tl.count[0];
+  } else {
+    // The four waves test a quarter each of up to 2048 requests at a time, their
+    // group ids loaded together: one memory round trip per 2048 requests.
+    const int entry = tid < nb ? tbl[b0 + tid] : 0;
+    for (int base = 0; base < a.R; base += W * kMemberSteps * kWave) {
+      const int left = a.R - base;
+      const int it = min(kMemberSteps, (left + W * kWave - 1) / (W * kWave));   // 64-request steps per wave
+      const int r0 = base + wave * it * kWave;
+      int x[kMemberSteps];
+#pragma unroll
+      for (int i = 0; i < kMemberSteps; ++i) x[i] = i < it ? a.gid[min(r0 + i * kWave + lane, a.R - 1)] : -1;
+      unsigned bits = 0;
+      int mine = 0;
+#pragma unroll
+      for (int i = 0; i < kMemberSteps; ++i) {
+        if (i < it) {
+          const bool is = reads(r0 + i * kWave + lane, x[i]);
+          bits |= (unsigned)is << i;
+          mine += __popcll(__ballot(is));
+        }
+      }
+      if (base > 0) __syncthreads();                   // the last round's counts are read
+      if (lane == 0) tl.count[wave] = mine;
+      __syncthreads();
+      int pos0 = total;
+#pragma unroll
+      for (int v = 0; v < W; ++v) {
+        const int n = tl.count[v];
+        total += n;
+        pos0 += v < wave ? n : 0;
+      }
+#pragma unroll
+      for (int i = 0; i < kMemberSteps; ++i) {
+        if (i < it) {
+          const bool is = (bits >> i) & 1u;
+          const unsigned long long mask = __ballot(is);
+          const int pos = pos0 + __popcll(mask & ((1ull << lane) - 1ull));
+          if (is && pos >= qbase && pos < qbase + W * 16) members[pos - qbase] = r0 + i * kWave + lane;
+          pos0 += __popcll(mask);
+        }
+      }
+    }
+    if (tid < nb) s_tbl[tid] = clampi(entry, 0, a.npblk - 1);
+    __syncthreads();
   }
-  __syncthreads();
-  const int nq = min(s_count - qbase, W * 16);
+  const int nq = min(total - qbase, W * 16);
   if (nq <= 0) return;                                 // uniform over the workgroup
   TileJob job;
   job.q = a.q; job.pk = a.pk; job.pv = a.pv; job.npool = a.npblk; job.H = H; job.h = h;

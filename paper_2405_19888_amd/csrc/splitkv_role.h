@@ -36,8 +36,22 @@ namespace parrot {
 // then issue while the current block is in flight) instead of vector loads.
 constexpr bool kStreamScalarTable = PARROT_SPLITKV_STREAM_SCALAR_TABLE != 0;
 
-// LDS bytes the split-KV role needs: six per-request arrays and a total.
-constexpr int kSplitkvLds = (6 * kMaxRequests + 4) * 4;
+// LDS bytes the split-KV role needs: two per-request arrays (six on the
+// per-request path) and a total per wave.
+constexpr int kSplitkvLds = (2 * kMaxRequests + kSkvWaves) * 4;
+static_assert((6 * kMaxRequestsPrefix + kSkvWaves) * 4 <= kSplitkvLds, "the per-request path's arrays fit");
+static_assert(kMaxRequests <= kWave * kWave, "two probes find a column's request");
+
+// Inclusive sum over the wave's lanes (DPP row shifts, then row broadcasts).
+PARROT_DEV int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);   // row_shr 1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);   // row_shr 2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);   // row_shr 4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);   // row_shr 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);   // row_bcast 15 into rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);   // row_bcast 31 into rows 2, 3
+  return x;
+}
 
 // One workgroup of the split-KV role; `wg` is the role-local workgroup index
 // and a.nwaves = 4 x (number of split-KV workgroups).
@@ -70,72 +84,92 @@ __device__ __forceinline__ void splitkv_role(const SplitKVArgs& a, char* lds, in
   constexpr int BLK_B = kBlock * ROW_B;
   static_assert(TPI * ROW_B == 1024, "one instruction covers 1 KiB");
 
-  // per-request data: first flat block per head-sequence, blocks per
-  // sequence, leading prefix blocks, group, prefix and own token counts
+  // per-request data: first flat block per head-sequence, own token counts and,
+  // on the per-request path, blocks per sequence, leading prefix blocks, group
+  // and prefix tokens
+  constexpr int MAXR = STREAM ? kMaxRequests : kMaxRequestsPrefix;
   int* s_excl = reinterpret_cast<int*>(lds);
-  int* s_cnt = s_excl + kMaxRequests;
-  int* s_nbp = s_cnt + kMaxRequests;
-  int* s_g = s_nbp + kMaxRequests;
-  int* s_plen = s_g + kMaxRequests;
-  int* s_slen = s_plen + kMaxRequests;
-  int& s_total = s_slen[kMaxRequests];
+  int* s_slen = s_excl + MAXR;
+  int* s_tot = s_slen + MAXR;                 // columns per scanning wave
+  int* s_cnt = s_tot + kSkvWaves;             // per-request path only from here on
+  int* s_nbp = s_cnt + MAXR;
+  int* s_g = s_nbp + MAXR;
+  int* s_plen = s_g + MAXR;
 
   const int lane = threadIdx.x & 63;
   const int wave_in_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int R = a.R, H = a.H;
 
-  if (wave_in_wg == 0) {
-    // Every request's own length (and, on the per-request path, its group and
-    // prefix length) is loaded before the scan: one memory round trip (two on
-    // the per-request path) instead of one per 64 requests.  Addresses are
-    // clamped into [0, R) so every load is unconditional.
-    constexpr int kIt = kMaxRequests / kWave;
-    int s_in[kIt], g_in[kIt], p_in[kIt];
+  {
+    // Wave v scans requests [v * per, (v + 1) * per): their own lengths (and, on
+    // the per-request path, groups and prefix lengths) are all loaded before the
+    // scan, one memory round trip (two on the per-request path) whatever R.
+    // Addresses are clamped into [0, R).  One wave scanning 1024 requests with
+    // shuffles through the LDS, and a second launch above 1024, cost 1000
+    // requests of 50 tokens (8 heads) 52.7 us against 48.3, 1500 requests in 24
+    // groups 370 us against 331 and 4000 of them 552 against 376 (member scan of
+    // the prefix role included).
+    constexpr int kIt = MAXR / kWave / kSkvWaves;
+    const int it = (R + kWave * kSkvWaves - 1) / (kWave * kSkvWaves);   // 64-request steps per wave, <= kIt
+    const int r0 = wave_in_wg * it * kWave;
+    int s_in[kIt], g_in[STREAM ? 1 : kIt], p_in[STREAM ? 1 : kIt];
 #pragma unroll
-    for (int i = 0; i < kIt; ++i) s_in[i] = a.slen[min(i * kWave + lane, R - 1)];
-    if (a.with_prefix) {
+    for (int i = 0; i < kIt; ++i) s_in[i] = i < it ? a.slen[min(r0 + i * kWave + lane, R - 1)] : 0;
+    if constexpr (!STREAM) {
 #pragma unroll
       for (int i = 0; i < kIt; ++i) {
-        const int g = a.gid[min(i * kWave + lane, R - 1)];
+        const int g = a.gid[min(r0 + i * kWave + lane, R - 1)];
         g_in[i] = (g >= 0 && g < a.NG) ? g : -1;
+        p_in[i] = 0;
       }
-#pragma unroll
-      for (int i = 0; i < kIt; ++i) p_in[i] = 0;
-      if (a.NG > 0) {                        // no prefix lengths exist without groups
+      if (a.NG > 0) {                          // no prefix lengths exist without groups
 #pragma unroll
         for (int i = 0; i < kIt; ++i) p_in[i] = a.plen[g_in[i] >= 0 ? g_in[i] : 0];
       }
     }
     int carry = 0;
+    int excl[kIt];
 #pragma unroll
     for (int i = 0; i < kIt; ++i) {
-      const int base = i * kWave;
-      if (base >= R) break;
-      const int r = base + lane;
-      const bool valid = r < R;
-      const int S = valid ? clampi(s_in[i], 0, a.max_s) : 0;
-      int g = -1, P = 0;
-      if (a.with_prefix && valid) {
-        g = g_in[i];
-        P = g >= 0 ? clampi(p_in[i], 0, a.max_p) : 0;
+      excl[i] = 0;
+      if (i < it) {                            // wave-uniform
+        const int r = r0 + i * kWave + lane;
+        const bool valid = r < R;
+        const int S = valid ? clampi(s_in[i], 0, a.max_s) : 0;
+        int cnt = (S + kBlock - 1) / kBlock;
+        if (valid) s_slen[r] = S;
+        if constexpr (!STREAM) {
+          const int g = valid ? g_in[i] : -1;
+          const int P = g >= 0 ? clampi(p_in[i], 0, a.max_p) : 0;
+          const int nbp = (P + kBlock - 1) / kBlock;
+          cnt += nbp;
+          if (valid) { s_cnt[r] = cnt; s_nbp[r] = nbp; s_g[r] = g; s_plen[r] = P; }
+        }
+        const int incl = wave_scan(cnt);
+        excl[i] = carry + incl - cnt;
+        if (valid) s_excl[r] = excl[i];
+        carry += __builtin_amdgcn_readlane(incl, kWave - 1);
       }
-      const int nbp = (P + kBlock - 1) / kBlock;
-      const int cnt = nbp + (S + kBlock - 1) / kBlock;
-      int incl = cnt;
-#pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        const int t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-      }
-      if (valid) {
-        s_excl[r] = carry + incl - cnt; s_cnt[r] = cnt; s_nbp[r] = nbp;
-        s_g[r] = g; s_plen[r] = P; s_slen[r] = S;
-      }
-      carry += __shfl(incl, kWave - 1);
     }
-    if (lane == 0) s_total = carry;
+    if (lane == 0) s_tot[wave_in_wg] = carry;
+    __syncthreads();
+    if (R > kWave) {                           // else wave 0 scanned them all
+      int before = 0;
+#pragma unroll
+      for (int v = 0; v < kSkvWaves - 1; ++v) before += v < wave_in_wg ? s_tot[v] : 0;
+#pragma unroll
+      for (int i = 0; i < kIt; ++i) {
+        const int r = r0 + i * kWave + lane;
+        if (i < it && r < R) s_excl[r] = before + excl[i];
+      }
+      __syncthreads();
+    }
   }
-  __syncthreads();
+  int s_total = 0;
+#pragma unroll
+  for (int v = 0; v < kSkvWaves; ++v) s_total += s_tot[v];
+  // block columns of request r's sequence
+  auto cols = [&](int r) { return STREAM ? (s_slen[r] + kBlock - 1) / kBlock : s_cnt[r]; };
   const int C = s_total;                                      // flat block columns
   const int HG = H / HPW;                                     // head groups (H % HPW == 0)
   const int G = a.nwaves / HG;                                // column groups
@@ -161,7 +195,7 @@ __device__ __forceinline__ void splitkv_role(const SplitKVArgs& a, char* lds, in
         for (int i = 0; i < kMaxDepth; ++i)
           if (i < nlev) np[nlev - 1 - i] = (clampi(a.plen[chain[i]], 0, a.max_p) + a.cp - 1) / a.cp;
       }
-      const int first = s_excl[rr], n = s_cnt[rr];
+      const int first = s_excl[rr], n = cols(rr);
       const int ns = n > 0 ? (first + n - 1) / Q - first / Q + 1 : 0;
       *reinterpret_cast<int4*>(a.merge_meta + kMetaInts * rr) =
           make_int4(ns, nlev, (int)((unsigned)np[0] | ((unsigned)np[1] << 16)),
@@ -176,15 +210,14 @@ __device__ __forceinline__ void splitkv_role(const SplitKVArgs& a, char* lds, in
   const int nblk_run = (C - c0 < Q) ? (C - c0) : Q;
 
   // the request holding column c0: the last request whose first column is <= c0
-  int r = 0;
-  for (int base = 0; base < R; base += kWave) {
-    const int rr = base + lane;
-    const unsigned long long mask = __ballot(rr < R && s_excl[rr] <= c0);
-    const int n = __popcll(mask);
-    if (n > 0) r = base + n - 1;
-    if (n < kWave) break;
-  }
-  int cnt = s_cnt[r];
+  // (lanes test every step-th request, then the requests of that step)
+  const int step = (R + kWave - 1) / kWave;                   // <= 64
+  const int probe = lane * step;
+  const int seg0 = (__popcll(__ballot(probe < R && s_excl[min(probe, R - 1)] <= c0)) - 1) * step;
+  const int cand = seg0 + lane;
+  int r = seg0 + __popcll(__ballot(lane < step && cand < R && s_excl[clampi(cand, 0, R - 1)] <= c0)) - 1;
+  r = clampi(r, 0, R - 1);                                    // in range whatever the data
+  int cnt = cols(r);
   if (cnt <= 0) return;                       // unreachable for consistent data
   int b = c0 - s_excl[r];
 
@@ -204,11 +237,11 @@ __device__ __forceinline__ void splitkv_role(const SplitKVArgs& a, char* lds, in
     size_t app_off;  // APPEND: pool byte offset of that piece for the first head
   };
   auto fetch = [&](Blk& B) {
-    const int nbp = s_nbp[r];
+    const int nbp = STREAM ? 0 : s_nbp[r];
     const char* kp;
     const char* vp;
     int entry, nblk, ntok;
-    if (b < nbp) {
+    if (!STREAM && b < nbp) {
       entry = (STREAM && !kStreamScalarTable) ? a.ptab[(long)s_g[r] * a.pstride + b]
                                               : ld_uniform(a.ptab + (long)s_g[r] * a.pstride + b);
       kp = (const char*)a.pk; vp = (const char*)a.pv; nblk = a.npblk;
@@ -257,8 +290,8 @@ __device__ __forceinline__ void splitkv_role(const SplitKVArgs& a, char* lds, in
     // advance the cursor to the next column (same head)
     if (++b == cnt) {
       b = 0;
-      do { ++r; } while (r < R && s_cnt[r] == 0);
-      cnt = r < R ? s_cnt[r] : 1;
+      do { ++r; } while (r < R && cols(r) == 0);
+      cnt = r < R ? cols(r) : 1;
     }
   };
 
