@@ -253,17 +253,22 @@ __global__ __launch_bounds__(NW * 64) void k_direct(DirectArgs a) {
   float mx = s_m[0];
 #pragma unroll
   for (int i = 1; i < NW; ++i) mx = fmaxf(mx, s_m[i]);
-  const float mref = (mx == -INFINITY) ? 0.f : mx;
+  // (no guard on mx: as in the merge, logits that are all -inf give NaN)
   float tot = 0.f, o = 0.f;
 #pragma unroll
   for (int i = 0; i < NW; ++i) {
-    const float c = fast_exp2(s_m[i] - mref);
+    const float c = fast_exp2(s_m[i] - mx);
     tot = __builtin_fmaf(c, s_l[i], tot);
     o = __builtin_fmaf(c, s_acc[i][d], o);
   }
-  // an empty context is defined as out = 0, lse = -inf
-  E::store1((char*)a.out + ((size_t)(x * H + h) * D + d) * E::kBytes, tot > 0.f ? o / tot : 0.f);
-  if (d == 0) a.lse[x * H + h] = tot > 0.f ? (mx + fast_log2(tot)) * kLn2 : -INFINITY;
+  // an empty context is defined as out = 0, lse = -inf; it is told by its length,
+  // since a sum that is not positive can also come from NaN or infinite inputs,
+  // which have to reach the output
+  bool empty = S <= 0;
+#pragma unroll
+  for (int l = 0; l < kMaxDepth; ++l) empty = empty && plen[l] <= 0;
+  E::store1((char*)a.out + ((size_t)(x * H + h) * D + d) * E::kBytes, empty ? 0.f : o / tot);
+  if (d == 0) a.lse[x * H + h] = empty ? -INFINITY : (mx + fast_log2(tot)) * kLn2;
 }
 
 template <int DT, int D, int NW>

@@ -93,3 +93,25 @@ def test_direct_append(dtype, D, heads):
     torch.cuda.synchronize()
     assert torch.equal(out, o2) and torch.equal(lse, l2)
     assert_close(*to_np(out, lse), *oracle_for(batch, plan), dtype, "direct append")
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("dtype,D", [("float16", 128), ("bfloat16", 64), ("float32", 64)])
+def test_direct_nonfinite(dtype, D, bad):
+    """NaN or infinite inputs reach the output and the log-sum-exp: only an empty
+    context gives 0 and -inf."""
+    print("[case] direct nonfinite", dtype, D, bad, flush=True)
+    plan = small_plan(dtype, D, 3, [-1, -1, -1, -1], seed=2)
+    batch = make_batch(plan, seed=7)
+    dev = batch.to("cuda")
+    r = len(OWN) - 1
+    dev["q"][r] = bad                       # every key of this request: NaN or mixed infinite logits
+    dec = Decoder(problem_for(plan))
+    dec.workspace.fill_(0xFF)
+    out, lse = dec(dev)
+    torch.cuda.synchronize()
+    assert bool(torch.all(dec.workspace == 0xFF).item()), "the two-kernel path ran"
+    assert bool(torch.isnan(out[r]).all()) and bool(torch.isnan(lse[r]).all())
+    rest = [i for i in range(plan.num_requests) if i != r]
+    want, want_lse = oracle_for(batch, plan)
+    assert_close(*to_np(out[rest], lse[rest]), want[rest], want_lse[rest], dtype, "direct nonfinite")
