@@ -20,9 +20,10 @@
 // 128-bit loads).  Each group of lanes that shares a token computes its slice
 // of q.k, the slices are summed with DPP row operations, and every token group
 // keeps its own online-softmax state; the groups are combined at the end of a
-// piece.  One block is reduced while the next one's loads are in flight; the
-// loop is unrolled by two with ping-pong registers and every load inside it is
-// unconditional, so the compiler's memory-wait counts stay exact.
+// piece.  One block is reduced while the next one's loads are in flight (not on
+// most fp32 paths, see the loop); the loop is unrolled by two with ping-pong
+// registers and every load inside it is unconditional, so the compiler's
+// memory-wait counts stay exact.
 #pragma once
 #include <type_traits>
 
@@ -407,15 +408,32 @@ __device__ __forceinline__ void splitkv_role(const SplitKVArgs& a, char* lds, in
     if (B.piece_end || run_end) close_piece(B.seq);
   };
 
-  Blk A, Bb;
-  fetch(A);
-  for (int i = 0;; i += 2) {
-    if (i + 1 >= nblk_run) { reduce(A, true); break; }
-    fetch(Bb);
-    reduce(A, false);
-    if (i + 2 >= nblk_run) { reduce(Bb, true); break; }
+  // A block of an fp32 cache is 64 registers (128-wide heads) or 32: two of them
+  // in ping-pong spilled to scratch at 128 (112 registers, some of them stored
+  // and reloaded for every block) and at 64 the streaming loop was slower too,
+  // so those run block by block.  On MI355X, ping-pong -> block by block:
+  // 128-wide, 200 requests of 10-300 own tokens on 300, 8 heads 84 -> 61 us, 80 of
+  // 300-900 on 600 108 -> 72, read per request 196 -> 97; 64-wide, the same two
+  // calls 37.6 -> 32.7 and 41.7 -> 38.9.  The per-request path keeps ping-pong at
+  // 64 (cached loads with scalar table entries keep two blocks in flight; 44.6 us
+  // block by block, 43.2 in ping-pong).
+  if constexpr (DT == kF32 && (STREAM || IPB > 4)) {
+    for (int i = 0; i < nblk_run; ++i) {
+      Blk A;
+      fetch(A);
+      reduce(A, i + 1 == nblk_run);
+    }
+  } else {
+    Blk A, Bb;
     fetch(A);
-    reduce(Bb, false);
+    for (int i = 0;; i += 2) {
+      if (i + 1 >= nblk_run) { reduce(A, true); break; }
+      fetch(Bb);
+      reduce(A, false);
+      if (i + 2 >= nblk_run) { reduce(Bb, true); break; }
+      fetch(A);
+      reduce(Bb, false);
+    }
   }
 }
 
