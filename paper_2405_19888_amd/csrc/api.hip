@@ -290,41 +290,77 @@ parrot_status no_merge(const parrot_trace& tr, hipStream_t s) {
 
 #define PARROT_TRY(x) do { parrot_status _s = (x); if (_s != PARROT_OK) return _s; } while (0)
 
+// `g_decode_path` (per thread, set through parrot_test_decode_path) overrides the
+// estimate below for tests and tuning: 0 two kernels; 1, 4 or 8 one launch (with
+// the rule's, four or eight waves per workgroup) wherever its lists fit.
+thread_local int g_decode_path = -1;
+
 // Waves per workgroup of the one-launch decode path (direct.hip), or 0 where the
-// partial-result and merge kernels are expected to be faster.  Both sides are
-// estimated in microseconds from the bounds in `p`, so every entry point makes
-// the same choice for the same problem; the figures are fits to sweeps on
-// MI355X (1-128 requests, prefixes of 0-2000 and own tokens of 20-3000, 5 to 32
-// heads, every dtype and head size):
-//  * two kernels: 9.3 us plus the bytes at 6.3 TB/s, each prefix read once (in
-//    fp32 the prefix role reaches 1.6 TB/s; on the per-request path every
-//    member's reads, at 17 TB/s from the caches);
-//  * one launch: 4.2 us, plus the longest context at 75 KB/us for its
-//    workgroup (rows under 512 bytes count as 512), or the own tokens at 5.4
-//    TB/s and every request's prefix reads at 17 TB/s from the L2 (6 where a
-//    head's workgroups do not share an XCD), plus 0.6 us per further workgroup
-//    of a CU.
-// Measured, two kernels / one, 32 heads: 8 requests of 300 tokens 12.5 / 9.1
-// us, 8 of 1000 24.2 / 22.5, 32 of 300 27.5 / 32.9; 8 on a 500-token prefix
-// 10.9 / 8.6, on a 2000-token one 14.7 / 18.6; 32 on a 500-token one 12.9 /
-// 19.3; five 64-wide heads, 40 requests on prefixes of 200-700: 10.8 / 12.4.
-int direct_waves(const parrot_problem* p, bool shared) {
+// partial-result and merge kernels are expected to be faster.  Every side is
+// estimated in microseconds from the bounds in `p`, so every entry point of a
+// path makes the same choice for the same problem.  The figures are fits to 620
+// calls on MI355X (1-128 requests over none, one, some or a group each, even and
+// ragged lengths of 1-4096 tokens, 4-40 heads, every dtype and head size, shared,
+// appending, nested and per request), each timed with its KV still in the 256 MB
+// cache and without:
+//  * bytes: a call reads the own tokens and each distinct prefix (at most one per
+//    request and level) from memory, whatever path it takes, and a prefix's other
+//    readers take it from the caches at 17-18 TB/s.  Lengths are bounds: the mean
+//    own length is taken as 0.56 of it, that of several prefixes as 0.82.
+//  * one launch: its longest context at 52 KB/us for a workgroup of eight waves
+//    (31 for four; rows under 512 bytes count as 512), or the bytes at 3.9 TB/s
+//    (3.8), whichever is longer: nothing balances ragged contexts.  4.1 us (3.9)
+//    without any, 2.0 us (1.35) more per further workgroup of a CU.
+//  * two kernels: 9.6 us, the bytes at 6.8 TB/s (fp32 prefixes 1.5, with 64-wide
+//    heads 2.3) or the first prefix chunk's chain (0.12 us a token in fp32, 0.08
+//    64-wide, 0.016 in 16 bits), and 0.15 us per piece of the longest own tokens
+//    that the merge reads.
+// Eight waves also above one workgroup per CU where their estimate is lower (257
+// to 512 workgroups of long contexts); four never below, where they are slower or
+// within 5 %.
+// Of 620 timed calls one is more than 3 % slower than on two kernels with its KV in
+// the cache, 25 (at most 22 %) with it in memory; on the whole 1.29x and 1.19x.
+// Measured, two kernels / one, 32 heads of 128, 16 bits: 8 requests of 300 tokens
+// 15.3 / 10.8 us, 8 of 1000 28.6 / 29.6, 32 of 300 33.1 / 40.0, 8 on one 500-token
+// prefix 10.9 / 9.3, on a 2000-token one 14.9 / 19.6, on four of 1000 18.7 / 16.0 (20.7
+// / 22.2 from memory), 4 on three of 3000 35.7 / 46.1; 29 on 22 of 1062, 40 heads,
+// 131 / 177; 39 on 20 of 2000, 8 heads, 47 / 62.
+int direct_waves(const parrot_problem* p, const parrot::Plan& pl, bool shared) {
   const int depth = p->num_groups > 0 ? std::max(1, (int)p->max_prefix_depth) : 0;
   const double pre = p->num_groups > 0 ? p->max_prefix_len : 0.0, own = p->max_suffix_len;
-  if (pre > parrot::kDirectMaxTokens || own > parrot::kDirectMaxTokens) return 0;
-  const bool f32 = p->dtype == PARROT_DTYPE_F32;
   const double R = p->num_requests, H = p->num_heads, cus = num_cus();
-  const double row = 2.0 * p->head_dim * (f32 ? 4.0 : 2.0);   // K and V of one token and head
-  const double own_bytes = R * own * H * row, member_bytes = R * depth * pre * H * row;
-  const double two = 9.3 + own_bytes / 6.3e6 +
-                     (shared ? p->num_groups * pre * H * row / (f32 ? 1.6e6 : 6.3e6) : member_bytes / 17e6);
   const double wgs = R * H;
-  const double one = 4.2 +
-                     std::max((depth * pre + own) * std::max(row, 512.0) / 75e3,
-                              own_bytes / 5.4e6 + member_bytes / (p->num_heads % 8 == 0 ? 17e6 : 6e6)) +
-                     0.6 * std::max(0.0, wgs / cus - 1.0);
-  if (wgs > 2e9 || one > 0.95 * two) return 0;
-  return wgs <= cus ? 8 : 4;
+  if (pre > parrot::kDirectMaxTokens || own > parrot::kDirectMaxTokens || wgs > 2e9 || g_decode_path == 0)
+    return 0;
+  if (g_decode_path > 1) return g_decode_path;
+  if (g_decode_path == 1) return wgs <= cus ? 8 : 4;
+
+  const bool f32 = p->dtype == PARROT_DTYPE_F32, wide = p->head_dim == 128;
+  const double row = 2.0 * p->head_dim * (f32 ? 4.0 : 2.0);   // K and V of one token and head
+  const double distinct = std::min((double)p->num_groups, R * depth);
+  const double own_tokens = R * own * (R > 1 ? 0.56 : 1.0);
+  const double pre_mean = pre * (distinct > 1 ? 0.82 : 1.0);
+  const double own_bytes = own_tokens * H * row, pre_bytes = distinct * pre_mean * H * row;
+  const double repeats = std::max(0.0, R * depth - distinct) * pre_mean * H * row;
+
+  const double longest = (depth * pre + own) * std::max(row, 512.0), more = std::max(0.0, wgs / cus - 1.0);
+  const double one8 = 4.1 + std::max(longest / 52e3, (own_bytes + pre_bytes) / 3.9e6 + repeats / 18e6) + 2.0 * more;
+  const double one4 = 3.9 + std::max(longest / 31e3, (own_bytes + pre_bytes) / 3.8e6 + repeats / 18e6) + 1.35 * more;
+
+  // column groups and columns of the split-KV role, and so pieces per sequence
+  const int hpw = splitkv_hpw(p, shared);
+  const double cols = (own_tokens + (shared ? 0.0 : R * depth * pre_mean)) / parrot::kBlock;
+  const double run = std::max((double)pl.skv_min_q, cols / splitkv_groups(p->num_heads, hpw));
+  const double pieces = (own + (shared ? 0.0 : pre)) / parrot::kBlock / run;
+  double two = 9.6 + 0.15 * pieces;
+  if (shared) {
+    const double chain = p->num_groups > 0 ? std::min(pre, (double)pl.cp) * (!f32 ? 0.016 : wide ? 0.12 : 0.08) : 0.0;
+    two += std::max(own_bytes / 6.8e6 + pre_bytes / (!f32 ? 6.8e6 : wide ? 1.5e6 : 2.3e6), chain);
+  } else {
+    two += (own_bytes + pre_bytes) / 6.8e6 + repeats / 17e6;
+  }
+  const int waves = wgs <= cus || one8 <= one4 ? 8 : 4;
+  return (waves == 8 ? one8 : one4) < two ? waves : 0;
 }
 
 // shared: prefix-group role for the prefixes (else the split-KV role reads
@@ -381,7 +417,7 @@ parrot_status decode(bool shared, const parrot_problem* p, const void* q, const 
   const float scale_log2 = p->sm_scale * parrot::kLog2e;
   const int D = p->head_dim, dt = (int)p->dtype;
 
-  if (const int waves = direct_waves(p, shared)) {
+  if (const int waves = direct_waves(p, pl, shared)) {
     parrot::DirectArgs a{};
     a.q = q; a.pk = prefix_k; a.pv = prefix_v; a.sk = suffix_k; a.sv = suffix_v;
     a.ptab = ptab; a.plen = plen; a.stab = stab; a.slen = slen; a.gid = gid;
@@ -542,6 +578,26 @@ parrot_status parrot_nested_prefix_decode(
                 prefix_lens, p && p->num_groups > 0 ? prefix_parents : nullptr,
                 suffix_block_tables, suffix_lens, group_ids, out, lse, workspace,
                 workspace_bytes, stream, trace);
+}
+
+}  // extern "C"
+
+// ------------------------------------------------------------- test hooks
+// Exported for tests and tuning, not declared in parrot_attn.h: the decode path
+// of this thread's calls (see g_decode_path; -1 gives the choice back to the
+// estimate), and the path a decode or prefill call with these arguments takes.
+extern "C" {
+
+void parrot_test_decode_path(int path) {
+  g_decode_path = path == 0 || path == 1 || path == 4 || path == 8 ? path : -1;
+}
+
+// Waves per workgroup of the one-launch kernel, 0 for two kernels, -1 for
+// invalid arguments.
+int parrot_test_decode_waves(const parrot_problem* p, int per_request) {
+  parrot::Plan pl;
+  if (check_problem(p, &pl) != PARROT_OK) return -1;
+  return p->num_requests == 0 ? 0 : direct_waves(p, pl, per_request == 0);
 }
 
 }  // extern "C"
@@ -926,6 +982,15 @@ int parrot_prefill_single_pass(const parrot_problem* p, const parrot_prefill_row
   if (check_prefill(p, rows, nested != 0, &pl) != PARROT_OK) return -1;
   g_err.clear();
   return pl.kind != parrot::kPrefillSplit ? 1 : 0;
+}
+
+// Test hook (not in parrot_attn.h): the plan a prefill takes (PrefillPlanKind; 16
+// is added to kPrefillRows with eight waves per workgroup), -1 for invalid
+// arguments.
+int parrot_test_prefill_plan(const parrot_problem* p, const parrot_prefill_rows* rows, int nested) {
+  PrefillPlan pl;
+  if (check_prefill(p, rows, nested != 0, &pl) != PARROT_OK) return -1;
+  return pl.kind + (pl.waves == 8 ? 16 : 0);
 }
 
 parrot_status parrot_shared_prefix_prefill(

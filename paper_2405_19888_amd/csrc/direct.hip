@@ -9,17 +9,19 @@
 // lane) beside the lengths, and the waves' results meet in LDS, which leaves
 // lengths, group, K/V and the store.  Every request reads its group's prefix
 // itself (repeats come from the caches; the workgroups of a head fall on one
-// XCD when the heads are a multiple of 8), so the host takes this path only
-// where those bytes are few (its rule carries the figures).
+// XCD when the heads are a multiple of 8), and nothing balances long contexts
+// against short ones, so the host takes this path only where an estimate of
+// both expects it to be faster (its rule carries the figures).
 //
-// Bound by round trips when the contexts are short (4.5 us a call, of which 3.4
-// an empty launch), then by what one CU draws from the caches (about 75 KB/us
-// per workgroup) and by the memory.  Measured, two kernels -> one: 4 fp32
-// requests of 150 tokens and 4 heads 9.1 -> 4.7 us; 7 chats of 40-700 tokens
-// with append, 32 heads 16.7 -> 11.1; 8 requests of 300 own tokens on a
-// 500-token prefix 15.5 -> 13.2.  Eight waves per workgroup up to one workgroup
-// per CU, four above (32 requests of 50 tokens: 11.3 us with eight, 9.6 with
-// four; the chats 11.1 with eight, 13.7 with four; sixteen are slower in both).
+// Bound by round trips when the contexts are short (4.4 us a call, of which 3.4
+// an empty launch), then by what one CU draws (about 75 KB/us per workgroup of
+// eight waves from the caches, 50 from memory) and by the memory.  Measured, two
+// kernels -> one: 4 fp32 requests of 150 tokens and 4 heads 9.0 -> 4.4 us; 7 chats
+// of 40-700 tokens with append, 32 heads 16.6 -> 11.3; 8 requests of 300 tokens
+// 15.3 -> 10.8.  Eight waves per workgroup up to one workgroup per CU, four above
+// unless long contexts make eight faster (32 requests of 50 tokens: 11.3 us with
+// eight, 9.6 with four; the chats 11.4 with eight, 13.2 with four; 9 requests of
+// 50-900 tokens 15.1 and 15.9; sixteen waves are slower in the first two).
 #include "common.h"
 
 namespace parrot {
