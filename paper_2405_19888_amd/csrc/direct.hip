@@ -61,13 +61,18 @@ __global__ __launch_bounds__(NW * 64) void k_direct(DirectArgs a) {
   const int col = w + NW * lane;
   int first = 0, count = 0;
   if constexpr (MODE == kDirectRows) {
-    // the row's request: the last one whose first row is at or before it
+    // the row's request: the last one whose first row is at or before it.  The
+    // lanes test every step-th request, then the requests of that step: a round
+    // trip per factor of 64 (8 rows of the last of 4096 requests, 8 heads: 6.1 us;
+    // walked 64 at a time 16.2).
     r = -1;
-    for (int base = 0; base < a.R; base += kWave) {
-      const int rr = base + lane;
-      const unsigned long long mask = __ballot(rr < a.R && a.qoff[min(rr, a.R - 1)] <= x);
-      if (mask != 0) r = base + 63 - __builtin_clzll(mask);
-      if (mask != ~0ull) break;
+    for (int base = 0, n = a.R; n > 0;) {
+      const int step = (n + kWave - 1) / kWave;
+      const int at = lane * step;
+      const int k = __popcll(__ballot(at < n && a.qoff[base + min(at, n - 1)] <= x));
+      if (k == 0 || step == 1) { r = base + k - 1; break; }
+      base += (k - 1) * step;
+      n = min(step, n - (k - 1) * step);
     }
     first = r >= 0 ? clampi(a.qoff[r], 0, a.T) : 0;
     const long n = r >= 0 ? (long)a.qoff[r + 1] - a.qoff[r] : 0;
