@@ -738,7 +738,9 @@ PrefillCosts prefill_costs(const parrot_problem* p, const parrot_prefill_rows* r
   const double own_stages = std::ceil(own / st), max_own = std::ceil(p->max_suffix_len / st);
   const double pre_stages = p->num_groups > 0 ? std::ceil(p->max_prefix_len / st) : 0.0;
   const double tiles_o = R * std::max(1.0, mean_q / tile + (mean_q > tile ? 0.5 : 0.0));
-  const double tiles_p = pl.qtiles_p > 0 ? std::max(T / tile + 0.5 * p->num_groups, (double)pl.qtiles_p) : 0.0;
+  // (groups that nobody reads make no tiles)
+  const double groups = std::min((double)p->num_groups, R * std::max(1, pl.depth));
+  const double tiles_p = pl.qtiles_p > 0 ? std::max(T / tile + 0.5 * groups, (double)pl.qtiles_p) : 0.0;
   // the longest tile alone and the load per CU hide most of each other
   auto both = [](double latency, double load) {
     return std::max(6.0 + latency, load) + 0.2 * std::min(6.0 + latency, load);
@@ -767,24 +769,38 @@ PrefillCosts prefill_costs(const parrot_problem* p, const parrot_prefill_rows* r
 
 // Estimated microseconds of a prefill without tiles (direct.hip: one workgroup
 // per row and head that reads the row's whole context), or -1 where it is not
-// built: as for the one-launch decode, plus the round trip that finds the row's
-// request and 0.9 us per further workgroup of a CU; repeated reads come from the caches at 22 TB/s (8 where a head's
-// workgroups spread over more than two XCDs).  The tiles' estimates run high
-// where everything waits on round trips (13.6 us measured for 21 estimated) and
-// low for the fp32 tile (18 and 33 us for 14 and 21), hence the factors at the
-// call.  Measured, tiles / rows: 4 fp32 requests of 16-32 rows on a 128-token
-// prefix, 4 heads 18.5 / 6.3 us; one fp16 request of 8-16 rows on 600 tokens, 4
-// heads 14.3 / 8.1; 16 of 1-4 rows on 100 tokens, 4 heads 9.3 / 5.4, 32 heads
-// 10.4 / 11.3; 4 of 8-16 rows on 100, 32 heads 9.5 / 11.7.
+// built.  As for the one-launch decode: 5 us, the longest context at 74 KB/us for
+// a workgroup of eight waves (42 for four), or the bytes, whichever is longer:
+// each distinct prefix and the own tokens of the requests that bring rows once
+// from memory at 5.6 TB/s, every further row's reads from the caches at 28 TB/s
+// (12.5 where a head's workgroups spread over more than two XCDs); 1.45 us per
+// further workgroup of a CU.  Lengths are bounds: the mean own length is taken as
+// 0.55 of it, that of several prefixes as 0.84.  Fitted to 240 calls of 1-64
+// requests of 1-300 rows, on none to a prefix each, timed with their KV in the
+// cache and without; the tiles' estimates run high where everything waits on
+// round trips (13.6 us measured for 21 estimated) and low for the fp32 tile (18
+// and 33 us for 14 and 21), hence the factors at the call.
+// Measured, tiles / rows: 4 fp32 requests of 16-32 rows on a 128-token prefix, 4
+// heads 18.5 / 6.3 us; one fp16 request of 8-16 rows on 600 tokens, 4 heads 14.3 /
+// 8.1; 16 of 1-4 rows on 100 tokens, 4 heads 9.3 / 5.4, 32 heads 10.4 / 11.3; 4 of
+// 8-16 rows on 100, 32 heads 9.5 / 11.7; two of 5 rows on a prefix of 1405 each, 32
+// 64-wide heads 15.9 / 19.6 (17.1 / 28.6 from memory); 5 of 14 rows, own 1054, 4
+// heads 13.8 / 18.0 (14.7 / 22.0).
 double direct_rows_cost(const parrot_problem* p, long T, int depth) {
   const double pre = p->num_groups > 0 ? p->max_prefix_len : 0.0, own = p->max_suffix_len;
   if (pre > parrot::kDirectMaxTokens || own > parrot::kDirectMaxTokens) return -1.0;
-  const double row = 2.0 * p->head_dim * (p->dtype == PARROT_DTYPE_F32 ? 4.0 : 2.0);
-  const double wgs = (double)T * p->num_heads, tokens = depth * pre + own;
-  return 4.6 +
-         std::max(tokens * std::max(row, 512.0) / 75e3,
-                  wgs * tokens * row / (p->num_heads % 4 == 0 || p->num_heads <= 2 ? 22e6 : 8e6)) +
-         0.9 * std::max(0.0, wgs / num_cus() - 1.0);
+  const double row = 2.0 * p->head_dim * (p->dtype == PARROT_DTYPE_F32 ? 4.0 : 2.0), R = p->num_requests;
+  const double wgs = (double)T * p->num_heads, cus = num_cus();
+  const double owners = std::min(R, (double)T);            // requests that bring rows, at most
+  const double prefixes = std::min((double)p->num_groups, owners * depth);
+  const double own_mean = own * (R > 1 ? 0.55 : 1.0), pre_mean = pre * (prefixes > 1 ? 0.84 : 1.0);
+  const double distinct = owners * own_mean + prefixes * pre_mean;   // tokens
+  const double repeats = std::max(0.0, T * (own_mean + depth * pre_mean) - distinct);
+  return 5.0 +
+         std::max((depth * pre + own) * std::max(row, 512.0) / (wgs <= cus ? 74e3 : 42e3),
+                  p->num_heads * row *
+                      (distinct / 5.6e6 + repeats / (p->num_heads % 4 == 0 || p->num_heads <= 2 ? 28e6 : 12.5e6))) +
+         1.45 * std::max(0.0, wgs / cus - 1.0);
 }
 
 parrot_status check_prefill(const parrot_problem* p, const parrot_prefill_rows* rows, bool nested,
@@ -841,15 +857,17 @@ parrot_status check_prefill(const parrot_problem* p, const parrot_prefill_rows* 
   if (can && (setting == 1 || setting == 2)) {
     pl->kind = setting;
   } else if (setting == -1 || setting == 3) {
-    // the tiled single-pass plans where they are expected to be clearly faster
+    // the tiled single-pass plans where they are expected to be faster (factors of
+    // 0.93-0.95 lose no call of the sweeps by more than 3 %; 0.9 left 59 requests of
+    // one row on split for 72 us, 61 stacked; 1.0 loses up to 1.21x)
     const PrefillCosts c = prefill_costs(p, rows, *pl);
     double best = c.split;
-    if (can && setting == -1 && std::min(c.stacked, c.direct) < 0.9 * c.split) {
+    if (can && setting == -1 && std::min(c.stacked, c.direct) < 0.95 * c.split) {
       best = std::min(c.stacked, c.direct);
       pl->kind = c.direct < c.stacked ? parrot::kPrefillDirect : parrot::kPrefillStacked;
     }
     const double one = direct_rows_cost(p, T, pl->depth);
-    if (one >= 0.0 && (setting == 3 || one < (p->dtype == PARROT_DTYPE_F32 ? 1.2 : 0.6) * best)) {
+    if (one >= 0.0 && (setting == 3 || one < (p->dtype == PARROT_DTYPE_F32 ? 1.45 : 0.6) * best)) {
       pl->kind = parrot::kPrefillRows;
       pl->waves = (double)T * H <= num_cus() ? 8 : 4;
     }

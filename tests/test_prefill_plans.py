@@ -1,5 +1,7 @@
 """Which plan prefill takes for calls of plain sizes (CPU: the choice reads host
 scalars only; 256 compute units are assumed without a GPU)."""
+import ctypes
+
 import pytest
 
 from paper_2405_19888_amd import binding as B
@@ -31,3 +33,36 @@ def test_plan_by_sizes(parrot_lib, kw, single, monkeypatch):
     monkeypatch.delenv("PARROT_PREFILL_SINGLE_PASS", raising=False)
     assert choice(**kw) == single
     assert not choice(**kw, nested=True) and not choice(**kw, dtype=0)
+
+
+SPLIT, STACKED, DIRECT, ROWS4, ROWS8 = 0, 1, 2, 3, 19       # ROWS8: eight waves per workgroup
+
+
+@pytest.mark.parametrize("kw,plan", [
+    # rows without tiles: the longest context and first reads of prefixes count
+    (dict(requests=4, heads=4, head_dim=64, prefix=128, own=32, total=96, most=32, dtype=0), ROWS4),   # 18.5 us / 6.3
+    (dict(requests=8, heads=8, prefix=200, own=40, total=8, most=1), ROWS8),                           # 14.1 / 5.9
+    (dict(requests=4096, heads=8, prefix=200, own=40, total=8, most=1), ROWS8),                        # 55.8 / 6.1
+    (dict(requests=2, heads=32, head_dim=64, groups=8, prefix=1405, own=5, total=10, most=5), SPLIT),  # 15.9 / 19.6
+    (dict(requests=5, heads=4, prefix=17, own=1054, total=73, most=15), SPLIT),                        # 13.8 / 18.0
+    # 57 of its groups unread
+    (dict(requests=3, heads=8, head_dim=64, groups=60, prefix=2593, own=371, total=33, most=11), SPLIT),  # 39.3 / 46.5
+    # one row each of 59 requests: 72 us split, 63 in tiles per request
+    (dict(requests=59, heads=20, groups=12, prefix=152, own=2555, total=59, most=1, group_rows=10), DIRECT),
+    (dict(requests=16, heads=32, prefix=100, own=64, total=640, most=64), DIRECT),                     # 24 / 26 / 15
+    (dict(requests=64, heads=32, prefix=600, own=64, total=2560, most=64), STACKED),                   # 104 / 59 / 84
+])
+def test_plan_kinds(parrot_lib, kw, plan, monkeypatch):
+    monkeypatch.delenv("PARROT_PREFILL_SINGLE_PASS", raising=False)
+    k = dict(dict(groups=1, dtype=1, head_dim=128), **kw)
+    prob = B.make_problem(
+        num_requests=k["requests"], num_heads=k["heads"], head_dim=k["head_dim"], block_size=16, num_groups=k["groups"],
+        max_group_size=1, max_prefix_len=k["prefix"], max_suffix_len=k["own"],
+        prefix_table_stride=-(-k["prefix"] // 16), suffix_table_stride=-(-k["own"] // 16),
+        num_prefix_blocks=65536, num_suffix_blocks=65536, dtype=k["dtype"], sm_scale=0.1)
+    rows = B.make_prefill_rows(k["total"], k["most"], k.get("group_rows", k["total"]))
+    assert parrot_lib.parrot_test_prefill_plan(ctypes.byref(prob), ctypes.byref(rows), 0) == plan
+    if plan == SPLIT:
+        assert not B.parrot_prefill_single_pass(prob, rows)
+    else:
+        assert B.parrot_prefill_single_pass(prob, rows)
