@@ -330,7 +330,8 @@ int direct_waves(const parrot_problem* p, const parrot::Plan& pl, bool shared) {
   const double pre = p->num_groups > 0 ? p->max_prefix_len : 0.0, own = p->max_suffix_len;
   const double R = p->num_requests, H = p->num_heads, cus = num_cus();
   const double wgs = R * H;
-  if (pre > parrot::kDirectMaxTokens || own > parrot::kDirectMaxTokens || wgs > 2e9 || g_decode_path == 0)
+  if (pre > parrot::kDirectMaxTokens || own > parrot::kDirectMaxTokens || wgs > parrot::kDirectMaxWgs ||
+      g_decode_path == 0)
     return 0;
   if (g_decode_path > 1) return g_decode_path;
   if (g_decode_path == 1) return wgs <= cus ? 8 : 4;
@@ -788,9 +789,9 @@ PrefillCosts prefill_costs(const parrot_problem* p, const parrot_prefill_rows* r
 // heads 13.8 / 18.0 (14.7 / 22.0).
 double direct_rows_cost(const parrot_problem* p, long T, int depth) {
   const double pre = p->num_groups > 0 ? p->max_prefix_len : 0.0, own = p->max_suffix_len;
-  if (pre > parrot::kDirectMaxTokens || own > parrot::kDirectMaxTokens) return -1.0;
-  const double row = 2.0 * p->head_dim * (p->dtype == PARROT_DTYPE_F32 ? 4.0 : 2.0), R = p->num_requests;
   const double wgs = (double)T * p->num_heads, cus = num_cus();
+  if (pre > parrot::kDirectMaxTokens || own > parrot::kDirectMaxTokens || wgs > parrot::kDirectMaxWgs) return -1.0;
+  const double row = 2.0 * p->head_dim * (p->dtype == PARROT_DTYPE_F32 ? 4.0 : 2.0), R = p->num_requests;
   const double owners = std::min(R, (double)T);            // requests that bring rows, at most
   const double prefixes = std::min((double)p->num_groups, owners * depth);
   const double own_mean = own * (R > 1 ? 0.55 : 1.0), pre_mean = pre * (prefixes > 1 ? 0.84 : 1.0);

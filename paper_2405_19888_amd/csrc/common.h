@@ -144,6 +144,7 @@ struct DirectArgs {
   float scale_log2;
 };
 constexpr int kDirectMaxTokens = 4096;   // per prefix level and of own tokens
+constexpr long kDirectMaxWgs = 1L << 22; // a launch holds less than 2^32 threads
 hipError_t launch_direct(const DirectArgs& a, int waves, int dtype, int D, hipStream_t s, hipEvent_t e0,
                          hipEvent_t e1);
 

@@ -303,7 +303,7 @@ hipError_t launch_direct(const DirectArgs& a, int waves, int dtype, int D, hipSt
   // a lane holds one table entry per list: at most 64 blocks per wave and list
   const int most = waves * kWave * kBlock;
   const long groups = (long)(a.qoff ? a.T : a.R) * a.H;
-  if (a.R < 1 || a.H < 1 || groups < 1 || groups > 0x7fffffffL || a.depth > kMaxDepth ||
+  if (a.R < 1 || a.H < 1 || groups < 1 || groups > kDirectMaxWgs || a.depth > kMaxDepth ||
       (waves != 4 && waves != 8) || a.max_s > most || (a.NG > 0 && a.max_p > most) || (a.qoff && a.k_new))
     return hipErrorInvalidValue;
   switch (dtype * 1000 + D) {

@@ -58,6 +58,8 @@ def test_forced_paths(parrot_lib):
         parrot_lib.parrot_test_decode_path(1)
         assert waves(parrot_lib, **large) == 4
         assert waves(parrot_lib, requests=2, heads=2, own=4097) == 0      # its lists do not fit
+        assert waves(parrot_lib, requests=1 << 17, heads=32, own=16) == 4
+        assert waves(parrot_lib, requests=1 << 18, heads=32, own=16) == 0  # nor one launch (2^32 threads)
         parrot_lib.parrot_test_decode_path(8)
         assert waves(parrot_lib, **large) == 8
     finally:

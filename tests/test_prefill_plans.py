@@ -66,3 +66,16 @@ def test_plan_kinds(parrot_lib, kw, plan, monkeypatch):
         assert not B.parrot_prefill_single_pass(prob, rows)
     else:
         assert B.parrot_prefill_single_pass(prob, rows)
+
+
+def test_rows_plan_stays_within_one_launch(parrot_lib, monkeypatch):
+    """Forced, the plan without tiles is left to calls whose workgroups one launch
+    can hold (less than 2^32 threads)."""
+    monkeypatch.setenv("PARROT_PREFILL_SINGLE_PASS", "3")
+    for total, plan in ((1 << 17, ROWS4), (1 << 18, SPLIT)):
+        prob = B.make_problem(
+            num_requests=1 << 12, num_heads=32, head_dim=64, block_size=16, num_groups=0, max_group_size=0,
+            max_prefix_len=0, max_suffix_len=100, prefix_table_stride=0, suffix_table_stride=7,
+            num_prefix_blocks=1, num_suffix_blocks=65536, dtype=0, sm_scale=0.1)
+        rows = B.make_prefill_rows(total, 100, 0)
+        assert parrot_lib.parrot_test_prefill_plan(ctypes.byref(prob), ctypes.byref(rows), 0) == plan
