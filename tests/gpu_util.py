@@ -2,12 +2,14 @@
 with the oracle at the stated tolerances.  No attention arithmetic here."""
 from __future__ import annotations
 
+import contextlib
+
 import numpy as np
 import torch
 
 import oracle
-from paper_2405_19888_amd import (Decoder, parrot_validate_inputs, parrot_validate_nested_inputs,
-                                  problem_from_host)
+from paper_2405_19888_amd import (Decoder, load_library, parrot_validate_inputs,
+                                  parrot_validate_nested_inputs, problem_from_host)
 from workloads.gen import TORCH_DTYPES
 
 # Tolerances: max |out_gpu - out_ref| over all elements (fp32-accumulated
@@ -57,6 +59,32 @@ def run_gpu(plan, dev: dict, shared: bool = True, problem=None, poison: bool = T
     out, lse = dec(dev, shared=shared, nested=nested)
     torch.cuda.synchronize()
     return out, lse
+
+
+@contextlib.contextmanager
+def decode_path(path: str):
+    """Force this thread's decode calls onto one path: "two" kernels (partial
+    results, merge), or "one" launch with the waves per workgroup of the rule, or
+    of "one4" / "one8" (small lists only; longer ones stay on two kernels)."""
+    force = load_library().parrot_test_decode_path
+    force({"two": 0, "one": 1, "one4": 4, "one8": 8}[path])
+    try:
+        yield
+    finally:
+        force(-1)
+
+
+def run_paths(plan, dev, shared=True, nested=None, problem=None):
+    """run_gpu on each decode path whose lists fit; yields (path, out, lse).  The
+    poisoned workspace shows which path ran: the one launch leaves it alone."""
+    prob = problem or problem_for(plan)
+    fits = max(prob.max_prefix_len, prob.max_suffix_len) <= 4096
+    for path in ("two", "one") if fits else ("two",):
+        with decode_path(path):
+            dec = Decoder(prob)
+            out, lse = run_gpu(plan, dev, shared=shared, problem=prob, decoder=dec, nested=nested)
+        assert bool((dec.workspace != 0xFF).any().item()) == (path == "two"), f"not the {path}-kernel path"
+        yield path, out, lse
 
 
 def to_np(out, lse):

@@ -64,7 +64,8 @@ def test_abi_version(parrot_lib):
 
 def test_batches_above_1024_requests_are_sized(parrot_lib):
     """No per-call request cap: decode and prefill size batches of any count
-    (the split-KV role streams them in slices of 1024 requests)."""
+    (the split-KV role streams them in slices, of 4096 requests on the shared
+    path and 1024 on the per-request path)."""
     for R in (1024, 1025, 2500, 20000):
         w = B.parrot_workspace_bytes(base_problem(num_requests=R))
         assert w >= R * 32 * 129 * 4, R

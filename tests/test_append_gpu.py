@@ -5,6 +5,7 @@ same call.  The oracle runs on pools that hold the new token in that slot.
 The slot the library writes is NaN before the call, so attending to the old
 contents (instead of k_new / v_new) shows up as a non-finite result.
 """
+import contextlib
 import math
 import sys
 
@@ -12,7 +13,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import assert_close, oracle_for, problem_for, to_np
+from gpu_util import assert_close, decode_path, oracle_for, problem_for, to_np
 from workloads import build_plan, get_config, make_batch, make_plan
 
 pytestmark = pytest.mark.gpu
@@ -36,9 +37,10 @@ def last_slots(plan):
     return out
 
 
-def run_append(plan, batch, seed=7):
-    """Poison the new tokens' slots, append through the library, and return
-    (out, lse, pools after the call, k_new, v_new, host pools with the token)."""
+def run_append(plan, batch, seed=7, path=None):
+    """Poison the new tokens' slots, append through the library (on the given
+    decode path, or the library's choice), and return (out, lse, pools after the
+    call, k_new, v_new, host pools with the token)."""
     from paper_2405_19888_amd import Decoder, parrot_validate_inputs
     g = torch.Generator().manual_seed(seed)
     R, H, D = plan.num_requests, plan.heads, plan.head_dim
@@ -64,8 +66,11 @@ def run_append(plan, batch, seed=7):
     dec.out.fill_(float("nan"))
     dec.lse.fill_(float("nan"))
     dec.workspace.fill_(0xFF)
-    out, lse = dec(dev, append=True)
+    with decode_path(path) if path else contextlib.nullcontext():
+        out, lse = dec(dev, append=True)
     torch.cuda.synchronize()
+    if path:
+        assert bool((dec.workspace != 0xFF).any().item()) == (path == "two"), f"not the {path}-kernel path"
     return out, lse, dev, k_new, v_new, kref, vref
 
 
@@ -95,14 +100,16 @@ def test_append_parity(kind, dtype, D):
     say("append", kind, dtype, D)
     plan = append_plan(kind, dtype, D)
     batch = make_batch(plan, seed=3)
-    out, lse, dev, k_new, v_new, kref, vref = run_append(plan, batch)
-    ref = oracle_for(batch, plan, pools=(kref, vref))
-    assert_close(*to_np(out, lse), *ref, dtype, f"append {kind} {dtype} D={D}")
-    # the cache now holds the new token in each request's last own slot, and
-    # nothing else changed
-    kp, vp = dev["k_pool"].cpu(), dev["v_pool"].cpu()
-    assert torch.equal(kp.nan_to_num(7.0), kref.nan_to_num(7.0))
-    assert torch.equal(vp.nan_to_num(7.0), vref.nan_to_num(7.0))
+    ref = None
+    for path in ("two", "one"):
+        out, lse, dev, k_new, v_new, kref, vref = run_append(plan, batch, path=path)
+        ref = ref or oracle_for(batch, plan, pools=(kref, vref))
+        assert_close(*to_np(out, lse), *ref, dtype, f"append {kind} {dtype} D={D} {path}")
+        # the cache now holds the new token in each request's last own slot, and
+        # nothing else changed
+        kp, vp = dev["k_pool"].cpu(), dev["v_pool"].cpu()
+        assert torch.equal(kp.nan_to_num(7.0), kref.nan_to_num(7.0))
+        assert torch.equal(vp.nan_to_num(7.0), vref.nan_to_num(7.0))
 
 
 def test_append_equals_write_then_decode():

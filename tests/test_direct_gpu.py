@@ -3,15 +3,16 @@ request and head attends to the whole context and writes the output) where its
 split can go wrong: contexts that end at a block, at the last wave's block (128
 tokens with eight waves, 64 with four) or one token to either side, empty own
 contexts, up to four prefix levels, both workgroup sizes, every entry point and
-dtype, against the oracle.  The poisoned workspace must come back untouched,
-which shows that the path ran."""
+dtype, against the oracle.  The path is forced where the choice by size is not
+the point; the poisoned workspace must come back untouched, which shows that it
+ran."""
 import math
 
 import numpy as np
 import pytest
 import torch
 
-from gpu_util import assert_close, oracle_for, problem_for, run_gpu, to_np
+from gpu_util import assert_close, decode_path, oracle_for, problem_for, run_gpu, to_np
 from paper_2405_19888_amd import Decoder, parrot_shared_prefix_decode_noalloc
 from workloads import build_plan, make_batch
 
@@ -46,15 +47,20 @@ def test_direct_parity(dtype, D, parents, heads):
     plan = small_plan(dtype, D, heads, parents)
     batch = make_batch(plan, seed=4)
     dev = batch.to("cuda")
-    out, lse = check(plan, dev, batch, what)
+    if heads == 24:          # eight waves above one workgroup per CU
+        with decode_path("one8"):
+            check(plan, dev, batch, what + " eight waves")
+    with decode_path("one"):
+        out, lse = check(plan, dev, batch, what)
     if not plan.nested:
-        check(plan, dev, batch, what + " per request", shared=False)
         o2, l2 = torch.empty_like(out), torch.empty_like(lse)
         prob = problem_for(plan)
-        parrot_shared_prefix_decode_noalloc(
-            prob, dev["q"], dev["k_pool"], dev["v_pool"], dev["k_pool"], dev["v_pool"],
-            dev["prefix_tables"], dev["prefix_lens"], dev["suffix_tables"], dev["suffix_lens"],
-            dev["group_ids"], o2, l2)
+        with decode_path("one"):
+            check(plan, dev, batch, what + " per request", shared=False)
+            parrot_shared_prefix_decode_noalloc(
+                prob, dev["q"], dev["k_pool"], dev["v_pool"], dev["k_pool"], dev["v_pool"],
+                dev["prefix_tables"], dev["prefix_lens"], dev["suffix_tables"], dev["suffix_lens"],
+                dev["group_ids"], o2, l2)
         torch.cuda.synchronize()
         assert torch.equal(out, o2) and torch.equal(lse, l2)
 
@@ -81,7 +87,8 @@ def test_direct_append(dtype, D, heads):
     dev["k_new"], dev["v_new"] = k_new, v_new
     dec = Decoder(problem_for(plan))
     dec.workspace.fill_(0xFF)
-    out, lse = dec(dev, append=True)
+    with decode_path("one"):
+        out, lse = dec(dev, append=True)
     torch.cuda.synchronize()
     assert bool(torch.all(dec.workspace == 0xFF).item()), "the two-kernel path ran"
     out, lse = out.clone(), lse.clone()
@@ -89,7 +96,8 @@ def test_direct_append(dtype, D, heads):
     as_int = torch.int32 if dtype == "float32" else torch.int16
     assert torch.equal(dev["k_pool"].view(as_int), want_k.view(as_int))
     assert torch.equal(dev["v_pool"].view(as_int), want_v.view(as_int))
-    o2, l2 = dec(dev)
+    with decode_path("one"):
+        o2, l2 = dec(dev)
     torch.cuda.synchronize()
     assert torch.equal(out, o2) and torch.equal(lse, l2)
     assert_close(*to_np(out, lse), *oracle_for(batch, plan), dtype, "direct append")
@@ -108,7 +116,8 @@ def test_direct_nonfinite(dtype, D, bad):
     dev["q"][r] = bad                       # every key of this request: NaN or mixed infinite logits
     dec = Decoder(problem_for(plan))
     dec.workspace.fill_(0xFF)
-    out, lse = dec(dev)
+    with decode_path("one"):
+        out, lse = dec(dev)
     torch.cuda.synchronize()
     assert bool(torch.all(dec.workspace == 0xFF).item()), "the two-kernel path ran"
     assert bool(torch.isnan(out[r]).all()) and bool(torch.isnan(lse[r]).all())

@@ -1,8 +1,10 @@
 """Batches above 1024 requests: the split-KV role streams them in slices of
-1024 requests (one launch each; the prefix-group role covers every request in
-the first launch, one merge follows).  2500 requests (slices 1024, 1024, 452)
-mixing grouped and ungrouped requests, against the oracle, on the shared,
-per-request, nested, appending and prefill entry points."""
+4096 requests on the shared path and of 1024 on the per-request path (one launch
+each; the prefix-group role covers every request in the first launch, one merge
+follows).  2500 requests (one slice; 1024, 1024 and 452 per request) mixing
+grouped and ungrouped requests, against the oracle, on the shared, per-request,
+nested, appending and prefill entry points; appending also with a second slice
+of 1 and of 904 requests, its groups spread over both."""
 import math
 import sys
 
@@ -24,16 +26,16 @@ def say(*a):
     sys.stdout.flush()
 
 
-def large_plan(dtype, nested=False, seed=0):
+def large_plan(dtype, nested=False, seed=0, requests=R):
     rng = np.random.default_rng(seed)
-    # groups of 1100 (spans two slices), 700, 300 and 1 members, the rest ungrouped
-    sizes = [1100, 700, 300, 1]
-    gor = [g for g, n in enumerate(sizes) for _ in range(n)] + [-1] * (R - sum(sizes))
+    # groups of 1100 (spans two slices), 700, 300 and 1 members of 2500, the rest ungrouped
+    sizes = [1100 * requests // R, 700 * requests // R, 300 * requests // R, 1]
+    gor = [g for g, n in enumerate(sizes) for _ in range(n)] + [-1] * (requests - sum(sizes))
     plen = [300, 517, 64, 33]
     parents = [-1, 0, -1, 2] if nested else None
     if nested:
         plen = [304, 517, 64, 33]                 # parents fill whole blocks
-    S = rng.integers(0, 90, size=R)
+    S = rng.integers(0, 90, size=requests)
     S[np.asarray(gor) < 0] += 1                   # ungrouped requests need a key
     return build_plan(heads=2, head_dim=128, block_size=16, dtype=dtype, group_of_request=gor,
                       prefix_lens=plen, suffix_lens=S.tolist(), sm_scale=1 / math.sqrt(128),
@@ -61,19 +63,20 @@ def test_nested_decode_above_1024_requests():
     assert_close(o, l, *ref, "float16", f"nested {R} requests")
 
 
-def test_append_above_1024_requests():
+@pytest.mark.parametrize("requests", [R, 4097, 5000])
+def test_append_above_1024_requests(requests):
     """Decode with append equals writing the new tokens first, then decoding,
     bit for bit, and writes every request's new token into its slot."""
     from paper_2405_19888_amd import Decoder
-    plan = large_plan("float16", seed=2)
-    say("append", R, "requests")
+    plan = large_plan("float16", seed=2, requests=requests)
+    say("append", requests, "requests")
     batch = make_batch(plan, seed=6)
     dev = batch.to("cuda")
     H, D = plan.heads, plan.head_dim
     g = torch.Generator(device="cuda").manual_seed(11)
-    k_new = torch.randn((R, H, D), generator=g, device="cuda").half()
-    v_new = torch.randn((R, H, D), generator=g, device="cuda").half()
-    have = [r for r in range(R) if plan.suffix_lens[r] > 0]
+    k_new = torch.randn((requests, H, D), generator=g, device="cuda").half()
+    v_new = torch.randn((requests, H, D), generator=g, device="cuda").half()
+    have = [r for r in range(requests) if plan.suffix_lens[r] > 0]
     blk = torch.tensor([int(plan.suffix_tables[r][(int(plan.suffix_lens[r]) - 1) // 16]) for r in have],
                        device="cuda")
     slot = torch.tensor([(int(plan.suffix_lens[r]) - 1) % 16 for r in have], device="cuda")

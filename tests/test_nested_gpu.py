@@ -13,7 +13,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import assert_close, oracle_for, problem_for, run_gpu, to_np
+from gpu_util import assert_close, oracle_for, problem_for, run_gpu, run_paths, to_np
 from workloads import build_plan, get_config, make_batch, make_device_layer, make_plan
 from workloads.gen import flatten_nested
 
@@ -73,8 +73,9 @@ def test_nested_parity(kind, dtype, D):
     say("nested", kind, dtype, D)
     plan = nested_plan(kind, dtype, D)
     batch = make_batch(plan, seed=2)
-    out, lse = run_gpu(plan, batch.to("cuda"))
-    assert_close(*to_np(out, lse), *oracle_for(batch, plan), dtype, f"nested {kind} {dtype} D={D}")
+    ref = oracle_for(batch, plan)
+    for path, out, lse in run_paths(plan, batch.to("cuda")):
+        assert_close(*to_np(out, lse), *ref, dtype, f"nested {kind} {dtype} D={D} {path}")
 
 
 def test_nested_entry_with_flat_groups_matches_flat_entry():

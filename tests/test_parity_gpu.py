@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import assert_close, oracle_for, problem_for, run_gpu, to_np
+from gpu_util import assert_close, oracle_for, problem_for, run_gpu, run_paths, to_np
 from workloads import build_plan, get_config, make_batch, make_plan
 
 pytestmark = pytest.mark.gpu
@@ -117,8 +117,8 @@ def test_edge_cases(kind, dtype, D):
     dev = batch.to("cuda")
     ref = oracle_for(batch, plan)
     for shared in (True, False):
-        out, lse = run_gpu(plan, dev, shared=shared)
-        assert_close(*to_np(out, lse), *ref, dtype, f"{kind} {dtype} D={D} shared={shared}")
+        for path, out, lse in run_paths(plan, dev, shared=shared):
+            assert_close(*to_np(out, lse), *ref, dtype, f"{kind} {dtype} D={D} shared={shared} {path}")
 
 
 def test_empty_batch_is_noop():
@@ -153,8 +153,8 @@ def test_separate_prefix_and_suffix_pools(dtype):
     dev2 = dict(dev, prefix_k=pk, prefix_v=pv, suffix_k=sk, suffix_v=sv)
     ref = oracle_for(batch, plan)
     for shared in (True, False):
-        out, lse = run_gpu(plan, dev2, shared=shared)
-        assert_close(*to_np(out, lse), *ref, dtype, f"separate pools shared={shared}")
+        for path, out, lse in run_paths(plan, dev2, shared=shared):
+            assert_close(*to_np(out, lse), *ref, dtype, f"separate pools shared={shared} {path}")
 
 
 # --------------------------------------------------------------------- probes
@@ -178,10 +178,10 @@ def test_zero_query_probe(dtype):
     N = plan.context_lens()
     assert np.allclose(ref_lse, np.log(N)[:, None], rtol=1e-12, atol=0)
     for shared in (True, False):
-        out, lse = run_gpu(plan, dev, shared=shared)
-        o, l = to_np(out, lse)
-        assert np.max(np.abs(l - ref_lse) / ref_lse) < 1e-6, f"shared={shared}"
-        assert np.max(np.abs(o - ref_out)) < (4e-3 if dtype == "bfloat16" else 5e-4)
+        for path, out, lse in run_paths(plan, dev, shared=shared):
+            o, l = to_np(out, lse)
+            assert np.max(np.abs(l - ref_lse) / ref_lse) < 1e-6, f"shared={shared} {path}"
+            assert np.max(np.abs(o - ref_out)) < (4e-3 if dtype == "bfloat16" else 5e-4)
 
 
 @pytest.mark.parametrize("dtype", ["float16", "bfloat16"])
@@ -211,14 +211,14 @@ def test_spike_probe(dtype):
                 k[blk, h, slot] = (c * qv).to(k.dtype)
             batch = type(base)(plan=plan, q=base.q, k_pool=k, v_pool=base.v_pool)
             dev = batch.to("cuda")
+            v = base.v_pool[blk, :, slot].double().numpy()
+            s = plan.sm_scale * (base.q[r].double() * k[blk, :, slot].double()).sum(-1).numpy()
             for shared in (True, False):
-                out, lse = run_gpu(plan, dev, shared=shared)
-                o, l = to_np(out, lse)
-                v = base.v_pool[blk, :, slot].double().numpy()
-                s = plan.sm_scale * (base.q[r].double() * k[blk, :, slot].double()).sum(-1).numpy()
-                assert np.max(np.abs(o[r] - v)) <= 1e-3 * max(1.0, np.abs(v).max()), \
-                    f"spike r={r} j={j} shared={shared}"
-                assert np.max(np.abs(l[r] - s) / np.abs(s)) < 1e-5, f"spike lse r={r} j={j}"
+                for path, out, lse in run_paths(plan, dev, shared=shared):
+                    o, l = to_np(out, lse)
+                    assert np.max(np.abs(o[r] - v)) <= 1e-3 * max(1.0, np.abs(v).max()), \
+                        f"spike r={r} j={j} shared={shared} {path}"
+                    assert np.max(np.abs(l[r] - s) / np.abs(s)) < 1e-5, f"spike lse r={r} j={j} {path}"
 
 
 # ------------------------------------------------------ scale and logit range
@@ -271,9 +271,9 @@ def test_scale_and_logit_range(kind, dtype):
     ref = oracle_for(batch, plan)
     dev = batch.to("cuda")
     for shared in (True, False):
-        out, lse = run_gpu(plan, dev, shared=shared)
-        assert_close(*to_np(out, lse), *ref, dtype, f"{kind} {dtype} shared={shared}",
-                     out_tol=6e-4 if loose else None, rel_l2=2e-4 if loose else None)
+        for path, out, lse in run_paths(plan, dev, shared=shared):
+            assert_close(*to_np(out, lse), *ref, dtype, f"{kind} {dtype} shared={shared} {path}",
+                         out_tol=6e-4 if loose else None, rel_l2=2e-4 if loose else None)
 
 
 # ------------------------------------------------------------ other properties

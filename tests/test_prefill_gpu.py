@@ -334,7 +334,7 @@ def test_prefill_single_pass_longest_ranges(dtype, D, monkeypatch):
 # 40) must become that row's output when the row sees it, and must not when
 # it lies after the row's position.
 
-PLANS = {"single": "1", "split": "0"}
+PLANS = {"single": "1", "split": "0", "direct": "2", "rows": "3"}
 
 
 def _prefix_len(plan, r):
@@ -343,7 +343,7 @@ def _prefix_len(plan, r):
 
 
 @pytest.mark.parametrize("dtype", ["float16", "bfloat16"])
-@pytest.mark.parametrize("path", ["single", "split"])
+@pytest.mark.parametrize("path", PLANS)
 def test_prefill_zero_query_probe(path, dtype, monkeypatch):
     from oracle.attention import prefill_positions
     monkeypatch.setenv("PARROT_PREFILL_SINGLE_PASS", PLANS[path])
@@ -355,7 +355,7 @@ def test_prefill_zero_query_probe(path, dtype, monkeypatch):
         q.zero_()
         keep = []
         out, lse = run_prefill(plan, device_dict(batch, q, off), off, keep=keep)
-        assert workspace_untouched(keep[0]) == (path == "single"), "unexpected prefill path"
+        assert workspace_untouched(keep[0]) == (path != "split"), "unexpected prefill path"
         ref_o, ref_l = oracle_prefill_for(batch, plan, q, off)
         n = np.array([_prefix_len(plan, r) + p + 1 for r, p in prefill_positions(off, plan.suffix_lens)])
         assert np.allclose(ref_l, np.log(n)[:, None], rtol=1e-12, atol=1e-15)
@@ -372,7 +372,10 @@ def test_prefill_zero_query_probe(path, dtype, monkeypatch):
 SCALE_CASES = ([(k, d, "split") for k in ("negative_scale", "zero_scale", "ramp")
                 for d in ("float16", "bfloat16", "float32")]
                + [(k, d, "single") for k in ("negative_scale", "zero_scale", "ramp")
-                  for d in ("float16", "bfloat16")])
+                  for d in ("float16", "bfloat16")]
+               + [("ramp", "float16", "direct"), ("negative_scale", "bfloat16", "direct"),
+                  ("ramp", "bfloat16", "rows"), ("ramp", "float32", "rows"),
+                  ("negative_scale", "float16", "rows")])
 
 
 @pytest.mark.parametrize("kind,dtype,path", SCALE_CASES)
@@ -407,7 +410,7 @@ def test_prefill_scale_and_logit_range(kind, dtype, path, monkeypatch):
         batch = type(batch)(plan=plan, q=batch.q, k_pool=k.to(td), v_pool=batch.v_pool)
     keep = []
     out, lse = run_prefill(plan, device_dict(batch, q, off), off, keep=keep)
-    assert workspace_untouched(keep[0]) == (path == "single"), "unexpected prefill path"
+    assert workspace_untouched(keep[0]) == (path != "split"), "unexpected prefill path"
     ref = oracle_prefill_for(batch, plan, q, off)
     # fp32 caches: logits near 200 carry about sqrt(D) 2^-24 200 = 1.4e-4 of
     # rounding from their fp32 dot products, and so does each weight relatively;
@@ -417,7 +420,7 @@ def test_prefill_scale_and_logit_range(kind, dtype, path, monkeypatch):
                  out_tol=6e-4 if loose else None, rel_l2=2e-4 if loose else None)
 
 
-@pytest.mark.parametrize("path", ["single", "split"])
+@pytest.mark.parametrize("path", PLANS)
 def test_prefill_spike_probe(path, monkeypatch):
     from oracle.attention import prefill_positions
     monkeypatch.setenv("PARROT_PREFILL_SINGLE_PASS", PLANS[path])
@@ -458,7 +461,7 @@ def test_prefill_spike_probe(path, monkeypatch):
                 assert np.max(np.abs(o[t] - v)) > 0.1, (t, j)
 
 
-@pytest.mark.parametrize("path", ["single", "split"])
+@pytest.mark.parametrize("path", PLANS)
 def test_prefill_bitwise_reproducible(path, monkeypatch):
     """The same inputs and plan give bitwise-identical output and lse (no
     atomics or order-dependent sums in either plan)."""

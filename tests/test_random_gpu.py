@@ -15,7 +15,7 @@ import sys
 import numpy as np
 import pytest
 
-from gpu_util import (assert_close, oracle_for, oracle_prefill_for, run_gpu, run_prefill, to_np)
+from gpu_util import (assert_close, oracle_for, oracle_prefill_for, run_paths, run_prefill, to_np)
 from workloads import build_plan, make_batch, make_prefill_queries
 
 pytestmark = pytest.mark.gpu
@@ -82,8 +82,8 @@ def test_random_decode(seed):
     dev = batch.to("cuda")
     ref = oracle_for(batch, plan)
     for shared in (True, False):
-        out, lse = run_gpu(plan, dev, shared=shared)
-        assert_close(*to_np(out, lse), *ref, plan.dtype, f"seed {seed} shared={shared}")
+        for path, out, lse in run_paths(plan, dev, shared=shared):
+            assert_close(*to_np(out, lse), *ref, plan.dtype, f"seed {seed} shared={shared} {path}")
 
 
 @pytest.mark.parametrize("seed", range(12))
@@ -92,8 +92,9 @@ def test_random_nested_decode(seed):
     say("random nested decode", seed, plan.dtype, "D", plan.head_dim, "H", plan.heads, "R",
         plan.num_requests, "parents", list(plan.prefix_parents))
     batch = make_batch(plan, seed=seed)
-    out, lse = run_gpu(plan, batch.to("cuda"))
-    assert_close(*to_np(out, lse), *oracle_for(batch, plan), plan.dtype, f"nested seed {seed}")
+    ref = oracle_for(batch, plan)
+    for path, out, lse in run_paths(plan, batch.to("cuda")):
+        assert_close(*to_np(out, lse), *ref, plan.dtype, f"nested seed {seed} {path}")
 
 
 @pytest.mark.parametrize("plan_path", ["split", "single"])
@@ -132,8 +133,10 @@ def test_random_append(seed):
     say("random append", seed, plan.dtype, "D", plan.head_dim, "H", plan.heads, "R",
         plan.num_requests)
     batch = make_batch(plan, seed=seed)
-    out, lse, dev, k_new, v_new, kref, vref = run_append(plan, batch, seed=seed)
-    ref = oracle_for(batch, plan, pools=(kref, vref))
-    assert_close(*to_np(out, lse), *ref, plan.dtype, f"append seed {seed}")
-    assert torch.equal(dev["k_pool"].cpu().nan_to_num(7.0), kref.nan_to_num(7.0))
-    assert torch.equal(dev["v_pool"].cpu().nan_to_num(7.0), vref.nan_to_num(7.0))
+    ref = None
+    for path in ("two", "one"):
+        out, lse, dev, k_new, v_new, kref, vref = run_append(plan, batch, seed=seed, path=path)
+        ref = ref or oracle_for(batch, plan, pools=(kref, vref))
+        assert_close(*to_np(out, lse), *ref, plan.dtype, f"append seed {seed} {path}")
+        assert torch.equal(dev["k_pool"].cpu().nan_to_num(7.0), kref.nan_to_num(7.0))
+        assert torch.equal(dev["v_pool"].cpu().nan_to_num(7.0), vref.nan_to_num(7.0))

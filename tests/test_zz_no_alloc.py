@@ -9,7 +9,8 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import assert_close, oracle_for, problem_for, run_gpu, to_np
+from gpu_util import assert_close, decode_path, oracle_for, problem_for, run_gpu, to_np
+from paper_2405_19888_amd import Decoder
 from workloads import build_plan, get_config, make_batch, make_plan
 
 pytestmark = pytest.mark.gpu
@@ -43,17 +44,21 @@ def _small_plan():
 
 def test_noalloc_matches_workspace_entry_twice():
     """C2 (LLaMA-7B layer, 1 x 32, P = 2048), then a 6-request batch: the
-    second call reuses the array the first one filled."""
-    for name, plan in (("llama7b_g32_p2048", make_plan(get_config("c2"))),
-                       ("small mixed batch", _small_plan())):
-        say("noalloc", name)
+    second call reuses the array the first one filled (both on two kernels; the
+    one launch, which uses no array, comes last)."""
+    for name, plan, path in (("llama7b_g32_p2048", make_plan(get_config("c2")), "two"),
+                             ("small mixed batch", _small_plan(), "two"),
+                             ("small mixed batch", _small_plan(), "one")):
+        say("noalloc", name, path)
         batch = make_batch(plan, seed=9)
         dev = batch.to("cuda")
-        ref_out, ref_lse = run_gpu(plan, dev, shared=True)
-        ref_out, ref_lse = ref_out.clone(), ref_lse.clone()
-        out, lse = _noalloc(plan, dev)
+        with decode_path(path):
+            dec = Decoder(problem_for(plan))
+            ref_out, ref_lse = run_gpu(plan, dev, shared=True, decoder=dec)
+            out, lse = _noalloc(plan, dev)
+        assert bool((dec.workspace != 0xFF).any().item()) == (path == "two")
         assert torch.equal(out, ref_out) and torch.equal(lse, ref_lse), name
-        assert_close(*to_np(out, lse), *oracle_for(batch, plan), plan.dtype, f"noalloc {name}")
+        assert_close(*to_np(out, lse), *oracle_for(batch, plan), plan.dtype, f"noalloc {name} {path}")
 
 
 def test_noalloc_rejects_batches_above_the_array():
