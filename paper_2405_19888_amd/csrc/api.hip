@@ -305,21 +305,21 @@ thread_local int g_decode_path = -1;
 // cache and without:
 //  * bytes: a call reads the own tokens and each distinct prefix (at most one per
 //    request and level) from memory, whatever path it takes, and a prefix's other
-//    readers take it from the caches at 17-18 TB/s.  Lengths are bounds: the mean
-//    own length is taken as 0.56 of it, that of several prefixes as 0.82.
+//    readers take it from the caches at 19-22 TB/s.  Lengths are bounds: the mean
+//    own length is taken as 0.46 of it, that of several prefixes as 0.64.
 //  * one launch: its longest context at 52 KB/us for a workgroup of eight waves
-//    (31 for four; rows under 512 bytes count as 512), or the bytes at 3.9 TB/s
-//    (3.8), whichever is longer: nothing balances ragged contexts.  4.1 us (3.9)
-//    without any, 2.0 us (1.35) more per further workgroup of a CU.
-//  * two kernels: 9.6 us, the bytes at 6.8 TB/s (fp32 prefixes 1.5, with 64-wide
-//    heads 2.3) or the first prefix chunk's chain (0.12 us a token in fp32, 0.08
-//    64-wide, 0.016 in 16 bits), and 0.15 us per piece of the longest own tokens
+//    (37 for four; rows under 512 bytes count as 512), or the bytes at 3.4 TB/s
+//    (3.3), whichever is longer: nothing balances ragged contexts.  4.2 us (3.9)
+//    without any, 2.3 us (1.2) more per further workgroup of a CU.
+//  * two kernels: 10 us, the bytes at 6.9 TB/s (fp32 prefixes 1.3, with 64-wide
+//    heads 4) or the first prefix chunk's chain (0.11 us a token in fp32, 0.064
+//    64-wide, 0.016 in 16 bits), and 0.17 us per piece of the longest own tokens
 //    that the merge reads.
 // Eight waves also above one workgroup per CU where their estimate is lower (257
 // to 512 workgroups of long contexts); four never below, where they are slower or
 // within 5 %.
-// Of 620 timed calls one is more than 3 % slower than on two kernels with its KV in
-// the cache, 25 (at most 22 %) with it in memory; on the whole 1.29x and 1.19x.
+// Of the 620 calls one is more than 3 % slower than on two kernels with its KV in
+// the cache and 31 (at most 17 %) with it in memory; on the whole 1.30x and 1.19x.
 // Measured, two kernels / one, 32 heads of 128, 16 bits: 8 requests of 300 tokens
 // 15.3 / 10.8 us, 8 of 1000 28.6 / 29.6, 32 of 300 33.1 / 40.0, 8 on one 500-token
 // prefix 10.9 / 9.3, on a 2000-token one 14.9 / 19.6, on four of 1000 18.7 / 16.0 (20.7
@@ -339,26 +339,26 @@ int direct_waves(const parrot_problem* p, const parrot::Plan& pl, bool shared) {
   const bool f32 = p->dtype == PARROT_DTYPE_F32, wide = p->head_dim == 128;
   const double row = 2.0 * p->head_dim * (f32 ? 4.0 : 2.0);   // K and V of one token and head
   const double distinct = std::min((double)p->num_groups, R * depth);
-  const double own_tokens = R * own * (R > 1 ? 0.56 : 1.0);
-  const double pre_mean = pre * (distinct > 1 ? 0.82 : 1.0);
+  const double own_tokens = R * own * (R > 1 ? 0.46 : 1.0);
+  const double pre_mean = pre * (distinct > 1 ? 0.64 : 1.0);
   const double own_bytes = own_tokens * H * row, pre_bytes = distinct * pre_mean * H * row;
   const double repeats = std::max(0.0, R * depth - distinct) * pre_mean * H * row;
 
   const double longest = (depth * pre + own) * std::max(row, 512.0), more = std::max(0.0, wgs / cus - 1.0);
-  const double one8 = 4.1 + std::max(longest / 52e3, (own_bytes + pre_bytes) / 3.9e6 + repeats / 18e6) + 2.0 * more;
-  const double one4 = 3.9 + std::max(longest / 31e3, (own_bytes + pre_bytes) / 3.8e6 + repeats / 18e6) + 1.35 * more;
+  const double one8 = 4.2 + std::max(longest / 52e3, (own_bytes + pre_bytes) / 3.4e6 + repeats / 22e6) + 2.3 * more;
+  const double one4 = 3.9 + std::max(longest / 37e3, (own_bytes + pre_bytes) / 3.3e6 + repeats / 22e6) + 1.2 * more;
 
   // column groups and columns of the split-KV role, and so pieces per sequence
   const int hpw = splitkv_hpw(p, shared);
   const double cols = (own_tokens + (shared ? 0.0 : R * depth * pre_mean)) / parrot::kBlock;
   const double run = std::max((double)pl.skv_min_q, cols / splitkv_groups(p->num_heads, hpw));
   const double pieces = (own + (shared ? 0.0 : pre)) / parrot::kBlock / run;
-  double two = 9.6 + 0.15 * pieces;
+  double two = 10.0 + 0.17 * pieces;
   if (shared) {
-    const double chain = p->num_groups > 0 ? std::min(pre, (double)pl.cp) * (!f32 ? 0.016 : wide ? 0.12 : 0.08) : 0.0;
-    two += std::max(own_bytes / 6.8e6 + pre_bytes / (!f32 ? 6.8e6 : wide ? 1.5e6 : 2.3e6), chain);
+    const double chain = p->num_groups > 0 ? std::min(pre, (double)pl.cp) * (!f32 ? 0.016 : wide ? 0.11 : 0.064) : 0.0;
+    two += std::max(own_bytes / 6.9e6 + pre_bytes / (!f32 ? 6.9e6 : wide ? 1.3e6 : 4.0e6), chain);
   } else {
-    two += (own_bytes + pre_bytes) / 6.8e6 + repeats / 17e6;
+    two += (own_bytes + pre_bytes) / 6.9e6 + repeats / 19e6;
   }
   const int waves = wgs <= cus || one8 <= one4 ? 8 : 4;
   return (waves == 8 ? one8 : one4) < two ? waves : 0;
