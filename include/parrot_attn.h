@@ -132,10 +132,11 @@ size_t parrot_workspace_bytes(const parrot_problem* p);
  *        16-token blocks over a fixed grid, with 128-bit coalesced streaming
  *        loads; one partial per (request, head) piece;
  *   2. the merge kernel: log-sum-exp combination of all partials of (r, h).
- * Small calls (few requests, short contexts; the same problem always decides
- * the same way) run as one kernel instead: a workgroup per (request, head)
- * attends to the whole context and writes the output, and the workspace stays
- * unused.  This holds for every decode entry point below.
+ * Small calls run as one kernel instead, where an estimate from the sizes in `p`
+ * expects it to be faster (the same problem always decides the same way): a
+ * workgroup per (request, head) attends to the whole context and writes the
+ * output, and the workspace stays unused.  This holds for every decode entry
+ * point below.
  *
  *   q                    [R][H][D] dtype, 16-byte aligned
  *   prefix_k, prefix_v   [num_prefix_blocks][H][B][D] dtype, 16-byte aligned
@@ -333,12 +334,13 @@ parrot_status parrot_validate_nested_inputs(
  *     kernel combines them per (row, head).
  * The split plan is left where an estimate from the sizes in `p` and `rows`
  * expects another to be faster; parrot_prefill_single_pass tells whether a call
- * writes its output directly.  The environment variable PARROT_PREFILL_SINGLE_PASS=0 forces the
- * split plan; =1 takes the single pass of stacked rows and =2 that of one
- * request per tile wherever the groups are flat, the caches 16-bit and the
- * lengths at most 8192, =3 the one without tiles wherever no prefix or own
- * length exceeds 4096; other values leave the choice to the estimate.  All
- * plans give the same results to rounding.
+ * writes its output directly.  The environment variable
+ * PARROT_PREFILL_SINGLE_PASS=0 forces the split plan; =1 takes the single pass
+ * of stacked rows and =2 that of one request per tile wherever the groups are
+ * flat, the caches 16-bit and the lengths at most 8192, =3 the one without tiles
+ * wherever no prefix or own length exceeds 4096 and T * H is at most 2^22; other
+ * values leave the choice to the estimate.  All plans give the same results to
+ * rounding.
  *
  *   rows                 (host) row counts; see parrot_prefill_rows
  *   q                    [T][H][D] dtype, 16-byte aligned

@@ -474,9 +474,9 @@ parrot_status decode(bool shared, const parrot_problem* p, const void* q, const 
     }
     // The split-KV role holds its per-request scan in LDS for up to 4096
     // requests (1024 on the per-request path), so a larger batch is streamed in
-    // slices of that many requests, one launch each (every per-request pointer moved to the
-    // slice); the prefix-group role covers every request in the first launch,
-    // and one merge follows.  The trace brackets all of them.
+    // slices of that many requests, one launch each (every per-request pointer
+    // moved to the slice); the prefix-group role covers every request in the
+    // first launch, and one merge follows.  The trace brackets all of them.
     const int R = p->num_requests, H = p->num_heads;
     const size_t elt = p->dtype == PARROT_DTYPE_F32 ? 4 : 2;
     const int most = shared ? parrot::kMaxRequests : parrot::kMaxRequestsPrefix;
@@ -685,8 +685,9 @@ struct PrefillPlan {
 // PARROT_PREFILL_SINGLE_PASS=0 turns the single-pass plans off; =1 takes the
 // stacked one and =2 the per-request one wherever the groups are flat, the
 // caches 16-bit and the ranges fit the tile's block table (8192 tokens), =3 the
-// one without tiles wherever no range exceeds 4096, for tests and tuning.  Any other value (or none) leaves the choice to the cost
-// estimate below.
+// one without tiles wherever no range exceeds 4096 and one launch holds its
+// workgroups, for tests and tuning.  Any other value (or none) leaves the choice
+// to the cost estimate below.
 int single_pass_setting() {
   const char* e = std::getenv("PARROT_PREFILL_SINGLE_PASS");
   if (e && e[0] >= '0' && e[0] <= '3' && e[1] == 0) return e[0] - '0';
@@ -711,8 +712,8 @@ int prefill_chunk(long len, double items_per_chunk) {
 //  * a workgroup alone on its CU takes 0.8 us per 16 KiB stage of keys, and up
 //    to three on a CU finish a stage every 0.28 + 0.05 w us together, w the
 //    waves with rows (0.33 with one, 0.48 with four);
-//  * a tile's set-up and output cost 1 + 0.9 w us of its CU (6 us of latency), each run of rows
-//    after a stacked tile's first 1 us (2.5 us of latency);
+//  * a tile's set-up and output cost 1 + 0.9 w us of its CU (6 us of latency),
+//    each run of rows after a stacked tile's first 1 us (2.5 us of latency);
 //  * a launch takes 5 us, the merge of the split plan 4 us more and its partial
 //    results (written, then read) pass at 4.5 TB/s (10 within the 256 MB cache).
 // Measured, split / stacked / per request: 16 requests of 16-64 rows on a

@@ -44,7 +44,7 @@
 // a request's heads run together, longest tiles of all heads first.  With one
 // request of 6000 tokens (188 tiles on 96 workgroup slots per XCD) the order
 // shortest first, head after head, left the last head's long tiles to run
-// alone: 370 -> 300 us (980 TFLOP/s); eight of 1000 tokens 119 -> 105 us.
+// alone: bf16 369 -> 306 us (960 TFLOP/s); eight of 1000 tokens 121 -> 106 us.
 #include "prefill_args.h"
 #include "prefill_tile.h"
 
